@@ -53,6 +53,7 @@ struct GemmArgs {
   long bstride;
   int splits;      // split-K factor (1 = none)
   float* partial;  // [splits][M][N] fp32 partial sums when splits > 1
+  int fixed_order;    // sum every output over k in the one order that does not depend on M
   int partials_only;  // with splits > 1: leave the sums and the epilogue to a later kernel
   int col0;        // first column of this launch in the full output (a launch over a column range; unsplit)
   void* out;       // EPI_STORE/_F32/_RESID: [M, N]; EPI_SWIGLU: [M, N/2]; EPI_QKV: queries [M, d_model]
@@ -85,6 +86,9 @@ struct AttnArgs {
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs& a, hipStream_t s);
 hipError_t launch_attention(int dtype, int head_dim, const AttnArgs& a, int n_tiles, hipStream_t s);
 // y row-major (row stride ldy) or, when ystride > 0, fragment-tiled.
+// fp32 GEMM on 16 x 32 tiles, where gemm_f32_small says so (unsplit).
+bool gemm_f32_small(int M, int N);
+hipError_t launch_gemm_f32_small(int epi, const GemmArgs& a, hipStream_t s);
 hipError_t launch_rmsnorm(int dtype, const void* x, int ldx, const int32_t* rows, const void* g, void* y, int ldy,
                           long ystride, int n_rows, int D, float eps, hipStream_t s);
 // Residual update from split-K partial sums followed by the RMSNorm of the updated rows:
@@ -130,7 +134,7 @@ inline long frag_astride(int Kp) { return (long)Kp * 32 + STRIDE_PAD_BYTES / 2; 
 __host__ __device__ inline size_t frag_off(int m, int k, long astride) {
   return (size_t)(m >> 5) * astride + (size_t)(k >> 4) * 512 + (size_t)(((m & 31) + ((k >> 3) & 1) * 32) * 8 + (k & 7));
 }
-int gemm_splits(int dtype, int M, int N, int Kp);  // split-K factor that fills the GPU
+int gemm_splits(int dtype, int epi, int M, int N, int Kp);  // split-K factor that fills the GPU
 int gemm_k_align();                  // K of the packed weights is a multiple of this
 
 constexpr int ATTN_BQ = 64;   // query rows per attention work tile

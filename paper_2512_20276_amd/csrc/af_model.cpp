@@ -469,15 +469,16 @@ GemmArgs gemm_args(int dtype, const void* A, int lda, long astride, const void* 
 }
 
 // fp32 elements of split-K partial sums a GEMM of this shape needs (0: no split).
-size_t split_need(const af_weights* w, int M, int N, int K) {
+size_t split_need(const af_weights* w, int epi, int M, int N, int K) {
   if (w->options & AF_OPT_NO_SPLIT_K) return 0;
-  const int S = gemm_splits(w->d.dtype, M, N, padk(K));
+  const int S = gemm_splits(w->d.dtype, epi, M, N, padk(K));
   return S > 1 ? (size_t)S * M * N : 0;
 }
 
-af_status with_splits(af_weights* w, Ws& ws, GemmArgs& g) {
-  if (!w || (w->options & AF_OPT_NO_SPLIT_K)) return AF_OK;
-  const int S = gemm_splits(w->d.dtype, g.M, g.N, g.Kp);
+af_status with_splits(af_weights* w, Ws& ws, int epi, GemmArgs& g) {
+  g.fixed_order = w->options & AF_OPT_NO_SPLIT_K ? 1 : 0;
+  if (g.fixed_order) return AF_OK;
+  const int S = gemm_splits(w->d.dtype, epi, g.M, g.N, g.Kp);
   if (S <= 1) return AF_OK;
   const size_t need = (size_t)S * g.M * g.N;
   if (need > ws.partial_cap) {
@@ -513,7 +514,7 @@ af_status step_qkv(af_weights* w, Ws& ws, int l, const void* xn, int ldx, long x
   g.head_dim = d.head_dim;
   g.n_heads = d.n_heads;
   g.max_pos = ring->d.max_pos;
-  AF_TRY(with_splits(w, ws, g));
+  AF_TRY(with_splits(w, ws, EPI_QKV, g));
   return timed(ws.timing, AF_K_GEMM_QKV, s, [&] { return launch_gemm(d.dtype, EPI_QKV, g, s); });
 }
 
@@ -547,7 +548,7 @@ af_status step_resid_proj(af_weights* w, Ws& ws, int cls, const void* A, int lda
   GemmArgs g = gemm_args(d.dtype, A, lda, as, W, M, d.d_model, K, hidden, d.d_model);
   g.resid = hidden;
   g.ldr = d.d_model;
-  AF_TRY(with_splits(w, ws, g));
+  AF_TRY(with_splits(w, ws, EPI_RESID, g));
   *normed = norm && g.splits > 1;
   if (!*normed) return timed(ws.timing, cls, s, [&] { return launch_gemm(d.dtype, EPI_RESID, g, s); });
   g.partials_only = 1;
@@ -571,7 +572,7 @@ af_status step_gate_up(af_weights* w, Ws& ws, int l, const void* xn, int ldx, lo
   const af_model_desc& d = w->d;
   GemmArgs g = gemm_args(d.dtype, xn, ldx, xs, w->layers[l].wgu, M, 2 * d.d_ff, d.d_model, act, ld_act);
   g.ostride = act_os;
-  AF_TRY(with_splits(w, ws, g));
+  AF_TRY(with_splits(w, ws, EPI_SWIGLU, g));
   return timed(ws.timing, AF_K_GEMM_GATEUP, s, [&] { return launch_gemm(d.dtype, EPI_SWIGLU, g, s); });
 }
 
@@ -622,7 +623,7 @@ af_status lm_head(af_weights* w, Ws& ws, const void* hidden, const DevTables& t,
   float* logits = out_logits ? out_logits : ws.logits;
   GemmArgs g = gemm_args(d.dtype, ws.emit_norm, w->ldD, w->xs_D, w->lm_head, t.n_emit, d.vocab, d.d_model, logits,
                          d.vocab);
-  AF_TRY(with_splits(w, ws, g));
+  AF_TRY(with_splits(w, ws, EPI_STORE_F32, g));
   AF_TRY(timed(ws.timing, AF_K_LM_HEAD, s, [&] { return launch_gemm(d.dtype, EPI_STORE_F32, g, s); }));
   if (out_tokens)
     AF_TRY(timed(ws.timing, AF_K_ARGMAX, s, [&] { return launch_argmax(logits, t.n_emit, d.vocab, out_tokens, s); }));
@@ -908,9 +909,11 @@ af_status af::packed_forward_in_buffer(af_weights* w, const int32_t* token_ids, 
   const size_t o_emit = take(act_bytes(w, std::max(n_emit, 1), false));
   const bool head = n_emit > 0 && (out_logits || out_tokens);
   const size_t o_logits = take(head && !out_logits ? (size_t)n_emit * d.vocab * 4 : 0);
-  size_t part = std::max({split_need(w, M, 3 * d.d_model, d.d_model), split_need(w, M, d.d_model, d.d_model),
-                          split_need(w, M, 2 * d.d_ff, d.d_model), split_need(w, M, d.d_model, d.d_ff)});
-  if (head) part = std::max(part, split_need(w, n_emit, d.vocab, d.d_model));
+  size_t part = std::max({split_need(w, EPI_QKV, M, 3 * d.d_model, d.d_model),
+                          split_need(w, EPI_RESID, M, d.d_model, d.d_model),
+                          split_need(w, EPI_SWIGLU, M, 2 * d.d_ff, d.d_model),
+                          split_need(w, EPI_RESID, M, d.d_model, d.d_ff)});
+  if (head) part = std::max(part, split_need(w, EPI_STORE_F32, n_emit, d.vocab, d.d_model));
   const size_t o_part = take(part * 4);
   if (off > buf_bytes) {
     set_error("af_packed_forward_noalloc: this step needs %zu bytes of scratch (M = %d, d_model %d, d_ff %d, "
@@ -1018,7 +1021,7 @@ extern "C" af_status af_op_linear(int32_t dtype, const void* x, const void* wt, 
   float* part = nullptr;
   if (e == hipSuccess) {
     GemmArgs g = gemm_args(dtype, xs ? xf : x, K, xs, wf, M, N, K, y, N);
-    g.splits = gemm_splits(dtype, M, N, Kp);  // the split the model path would use for this shape
+    g.splits = gemm_splits(dtype, EPI_STORE, M, N, Kp);  // the split the model path would use for this shape
     if (g.splits > 1) {
       e = hipMalloc((void**)&part, (size_t)g.splits * M * N * 4);
       g.partial = part;

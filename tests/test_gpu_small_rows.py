@@ -1,0 +1,37 @@
+"""GPU parity of the projection GEMMs for few rows at the edges of their tiles.
+
+fp32 projections of up to 1024 tiles of 16 x 32 run on those.  Every element is held to what its arithmetic allows: fp32 sums of
+K products in any order lie within K 2^-24 sum |x w| of the exact value, and storing in bf16 adds
+at most 2^-8 of it.
+"""
+import pytest
+import torch
+
+import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+af = pytest.importorskip("paper_2512_20276_amd")
+
+
+def _check(M, N, K, dt):
+    x = wl.draw(("t_rows_x", M, K), (M, K), dtype=dt, device="cuda")
+    w = wl.draw(("t_rows_w", N, K), (N, K), std=0.02, dtype=dt, device="cuda")
+    y = torch.full((M, N), float("nan"), dtype=dt, device="cuda")
+    af.op_linear(x, w, y)
+    torch.cuda.synchronize()
+    xd, wd = x.cpu().double(), w.cpu().double()
+    ref = xd @ wd.t()
+    bound = (K + 8) * 2.0 ** -24 * (xd.abs() @ wd.abs().t())
+    if dt == torch.bfloat16:
+        bound = bound + ref.abs() * 2.0 ** -8
+    err = (y.cpu().double() - ref).abs()
+    assert bool((err <= bound).all()), (M, N, K, float((err - bound).max()))
+
+
+@pytest.mark.parametrize("M", [1, 15, 16, 17, 34, 200])
+@pytest.mark.parametrize("N,K", [(16, 4), (48, 252), (768, 256), (256, 688), (1376, 260), (512, 1600)])
+def test_f32_small_tiles(M, N, K):
+    """Row and column remainders of the 16 x 32 tile; K below, at and past what a wave requests at
+    once (two steps of 32 at K <= 256, six beyond, and more than one such share)."""
+    _check(M, N, K, torch.float32)
