@@ -1024,6 +1024,12 @@ static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) 
   if (a.astride <= 0 || a.Kp % 256 != 0 || a.astride < (long)a.Kp * 32 || a.bstride < (long)a.Kp * 32)
     return hipErrorInvalidValue;
   hipError_t e;
+  StreamPlan sp;
+  if (!a.fixed_order && stream_plan(a.M, a.N, a.Kp, epi, &sp) && sp.splits == a.splits) {
+    e = launch_gemm_stream(sp, epi, a, s);
+    if (e != hipSuccess || a.splits <= 1 || a.partials_only) return e;
+    return reduce_launch<bf16>(epi, a, s);
+  }
   if (use_c6(epi, a)) {
     e = gemm32c_launch(epi, a, s);
     if (e != hipSuccess || a.splits <= 1 || a.partials_only) return e;
@@ -1055,6 +1061,8 @@ static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) 
 
 int gemm_splits(int dtype, int epi, int M, int N, int Kp) {
   if (dtype == AF_BF16) {
+    StreamPlan sp;
+    if (stream_plan(M, N, Kp, epi, &sp)) return sp.splits;
     if (const int S = c6_narrow(M, N, Kp)) return S;
     if (const int S = c6_wide_splits(M, N, Kp)) return S;
     const int fm = fm_for(M);

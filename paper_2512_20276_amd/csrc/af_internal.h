@@ -86,6 +86,13 @@ struct AttnArgs {
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs& a, hipStream_t s);
 hipError_t launch_attention(int dtype, int head_dim, const AttnArgs& a, int n_tiles, hipStream_t s);
 // y row-major (row stride ldy) or, when ystride > 0, fragment-tiled.
+// bf16 GEMM with the K range split over a workgroup's waves, for up to STREAM_MAX_M rows.
+constexpr int STREAM_MAX_M = 192;
+struct StreamPlan {
+  int fm, cb, splits;  // 32-row blocks, 32-column blocks per tile, K splits over workgroups
+};
+bool stream_plan(int M, int N, int Kp, int epi, StreamPlan* p);
+hipError_t launch_gemm_stream(const StreamPlan& p, int epi, const GemmArgs& a, hipStream_t s);
 // fp32 GEMM on 16 x 32 tiles, where gemm_f32_small says so (unsplit).
 bool gemm_f32_small(int M, int N);
 hipError_t launch_gemm_f32_small(int epi, const GemmArgs& a, hipStream_t s);

@@ -1,6 +1,8 @@
 """GPU parity of the projection GEMMs for few rows at the edges of their tiles.
 
-fp32 projections of up to 1024 tiles of 16 x 32 run on those.  Every element is held to what its arithmetic allows: fp32 sums of
+bf16 up to 192 rows runs with K split over a workgroup's waves (one kernel instance per number of
+32-row blocks, tiles of 1 to 4 column blocks, 1 to 8 K splits); fp32 projections of up to 1024
+tiles of 16 x 32 run on those.  Every element is held to what its arithmetic allows: fp32 sums of
 K products in any order lie within K 2^-24 sum |x w| of the exact value, and storing in bf16 adds
 at most 2^-8 of it.
 """
@@ -27,6 +29,22 @@ def _check(M, N, K, dt):
         bound = bound + ref.abs() * 2.0 ** -8
     err = (y.cpu().double() - ref).abs()
     assert bool((err <= bound).all()), (M, N, K, float((err - bound).max()))
+
+
+@pytest.mark.parametrize("M", [1, 2, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193])
+@pytest.mark.parametrize("N,K", [(48, 256), (608, 4096), (4096, 1024)])
+def test_bf16_row_block_edges(M, N, K):
+    """Every instance's first and last row count; a last column block half past N (48), tiles past
+    the last column block (608 = 19 blocks), split and unsplit K."""
+    _check(M, N, K, torch.bfloat16)
+
+
+@pytest.mark.parametrize("M", [7, 135, 192])
+@pytest.mark.parametrize("N,K", [(4096, 11008), (12288, 4096), (22016, 256), (32000, 512)])
+def test_bf16_projection_widths(M, N, K):
+    """The 7B projections' widths with their K splits (11008: shares of 43 k units), and widths
+    that take three and four column blocks per tile."""
+    _check(M, N, K, torch.bfloat16)
 
 
 @pytest.mark.parametrize("M", [1, 15, 16, 17, 34, 200])
