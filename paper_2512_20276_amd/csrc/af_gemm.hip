@@ -555,182 +555,6 @@ __global__ __launch_bounds__(256, 1) void gemm32x2_kernel(GemmArgs a) {
   }
 }
 
-// Wide tile for many rows: 32 FM rows x 32 CB NW columns on NW waves, each owning CB 32-column
-// weight blocks over all FM row blocks (as gemm32c_kernel does for 160 rows), so no weight
-// fragment is loaded twice.  Per byte loaded into the CU the 288 x 256 tile does 1.5x the MFMA
-// work of the 288 x 128 one (288 + 256 bytes per row of K for 288 x 256 outputs, against
-// 288 + 128 for 288 x 128).  Every activation fragment read from LDS feeds CB MFMAs: with
-// eight waves of one block each (two waves per SIMD, 144 accumulator registers) the LDS reads
-// of a 16-k step (72 KB) take as long as its MFMAs; with four waves of two blocks (one wave per
-// SIMD, 288 accumulator registers) they take half, and each wave double-buffers its
-// fragments, as no other wave on its SIMD covers the LDS latency.  The weights run two k steps
-// ahead.  Activations by DMA from waves 0..3; the fp32 tile goes through the LDS ring three
-// row blocks per pass.  (Three row groups of four column groups, each wave two weight blocks,
-// measured no faster: each weight fragment was then requested once per row group.  Four
-// waves of two blocks, 256 x 256 with 256 accumulator registers, measured 1.2x slower for
-// gate/up at 2264 rows: one wave per SIMD leaves every wait of a wave on the matrix core.)
-template <int FM, int NW, int CB, int EPI>
-__global__ __launch_bounds__(64 * NW, 1) void gemm32w_kernel(GemmArgs a) {
-  constexpr int KS = 4, NBUF = 4, PFB = 2, BLK = 512, TN = 32 * CB * NW, PB = 3;
-  constexpr int AFB = NW <= 4 ? 2 : 1;  // activation fragment buffers per wave
-  constexpr int SB = FM * KS;           // fragment blocks per stage
-  constexpr int DW = SB / 4;            // DMAs per stage of each of waves 0..3
-  constexpr int NPASS = (FM + PB - 1) / PB;
-  static_assert(SB % 4 == 0 && KS % PFB == 0 && NW >= 4, "pipeline shape");
-  __shared__ __attribute__((aligned(1024))) bf16 As[NBUF][SB * BLK];
-  static_assert(32 * PB * TN * 4 <= (int)sizeof(As), "an epilogue pass must fit the stage buffers");
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n_blocks = (a.N + 31) >> 5, n_nt = (n_blocks + NW * CB - 1) / (NW * CB);
-  const int m_blocks = (a.M + 31) >> 5, n_mt = (m_blocks + FM - 1) / FM;
-  const int S = a.splits;
-  const int t = xcd_remap(blockIdx.x, n_mt * n_nt * S);
-  const int mt = t % n_mt, rest = t / n_mt;
-  const int sp = rest % S, nt = rest / S;
-  const int ks16 = a.Kp >> 4;
-  const int units = ks16 / (KS * NBUF), per = (units + S - 1) / S;
-  const int kb = min(units, sp * per) * (KS * NBUF), ke = min(units, sp * per + per) * (KS * NBUF);
-  const int n_st = (ke - kb) / KS;  // a multiple of NBUF
-  // this wave's weight blocks (past N: a valid block whose columns are never stored)
-  const bf16* bp[CB];
-  static_for<0, CB>([&](auto c) {
-    bp[c] = (const bf16*)a.B + (size_t)min((nt * NW + wave) * CB + (int)decltype(c)::value, n_blocks - 1) * a.bstride +
-            lane * 8;
-  });
-  const bf16* __restrict__ Ab = (const bf16*)a.A;
-  float* T_ = (float*)&As[0][0];
-  const int m0 = mt * FM * 32, n0 = nt * TN;
-
-  auto body = [&](auto d_c) {
-    constexpr int D = decltype(d_c)::value;  // DMAs per stage issued by this wave
-    auto dma = [&](auto buf, int st) {
-      static_for<0, D>([&](auto d) {
-        const int q = wave + 4 * decltype(d)::value, mb = q / KS, j = q % KS;
-        const int k = min(kb + st * KS + j, ks16 - 1);
-        const int blk = min(mt * FM + mb, m_blocks - 1);  // rows past M: a valid block, never stored
-        const bf16* src = Ab + (size_t)blk * a.astride + (size_t)k * BLK + lane * 8;
-        __builtin_amdgcn_global_load_lds((const void*)src,
-                                         (__attribute__((address_space(3))) void*)&As[buf][q * BLK], 16, 0, 0);
-      });
-    };
-    bf16x8 rb[PFB][CB];
-    auto load_b = [&](auto slot, int st, int j) {
-      const int k = min(kb + st * KS + j, ks16 - 1);
-      static_for<0, CB>([&](auto c) {
-        const bf16* src = bp[c] + (size_t)k * BLK;
-        bf16x8 v;
-        asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(v) : "v"(src) : "memory");
-        rb[slot][c] = v;
-      });
-    };
-    f32x16 acc[FM][CB];
-    static_for<0, FM>([&](auto i) { static_for<0, CB>([&](auto c) { acc[i][c] = f32x16{}; }); });
-    static_for<0, NBUF - 1>([&](auto b) {
-      dma(b, b);
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    static_for<0, PFB>([&](auto j) { load_b(std::integral_constant<int, decltype(j)::value>{}, 0, j); });
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loop's waits count from a full ring
-    __builtin_amdgcn_sched_barrier(0);
-    for (int st0 = 0; st0 < n_st; st0 += NBUF) {
-      static_for<0, NBUF>([&](auto u) {
-        constexpr int U = decltype(u)::value;
-        const int st = st0 + U;
-        // Loads complete in order.  Stage st's activations come from the DMA at the top of stage
-        // st - NBUF + 1, after which NBUF - 1 stages of weight loads (CB KS each) and NBUF - 2
-        // DMAs were issued.  k step j's weights were loaded PFB steps earlier; after them came
-        // the CB (PFB - 1) weight loads of the steps between and, when a stage top lies between,
-        // its DMAs.
-        constexpr int WAIT_A = CB * KS * (NBUF - 1) + D * (NBUF - 2);
-        static_assert(WAIT_A <= 63, "vmcnt range");
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(WAIT_A) : "memory");
-        dma(std::integral_constant<int, (U + NBUF - 1) % NBUF>{}, st + NBUF - 1);
-        __builtin_amdgcn_sched_barrier(0);
-        bf16x8 af[AFB][FM];
-        if constexpr (AFB == 2) {
-          static_for<0, FM>([&](auto i) {
-            af[0][i] = *(const bf16x8*)(&As[U][((int)decltype(i)::value * KS) * BLK + lane * 8]);
-          });
-        }
-        static_for<0, KS>([&](auto j) {
-          constexpr int J = decltype(j)::value;
-          constexpr int slot = (U * KS + J) % PFB;
-          constexpr int CUR = AFB == 2 ? (J & 1) : 0;
-          if constexpr (AFB == 2) {  // the next k step's fragments, read while these MFMAs run
-            if constexpr (J + 1 < KS) {
-              static_for<0, FM>([&](auto i) {
-                af[(J + 1) & 1][i] = *(const bf16x8*)(&As[U][((int)decltype(i)::value * KS + J + 1) * BLK + lane * 8]);
-              });
-            }
-          } else {
-            static_for<0, FM>([&](auto i) {
-              af[0][i] = *(const bf16x8*)(&As[U][((int)decltype(i)::value * KS + J) * BLK + lane * 8]);
-            });
-          }
-          constexpr int WAIT_B = CB * (PFB - 1) + (J < PFB ? D : 0);
-          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(WAIT_B) : "memory");
-          __builtin_amdgcn_sched_barrier(0);
-          static_for<0, FM>([&](auto i) {
-            static_for<0, CB>([&](auto c) {
-              acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[CUR][i], rb[slot][c], acc[i][c], 0, 0, 0);
-            });
-          });
-          load_b(std::integral_constant<int, slot>{}, st + (J + PFB) / KS, (J + PFB) % KS);
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      });
-    }
-    // the ring's last (unused) loads land before any of its registers can be reused
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int p = 0; p < PFB; ++p)
-#pragma unroll
-      for (int c = 0; c < CB; ++c) asm volatile("" : "+v"(rb[p][c]));
-
-    // ---- epilogue, PB row blocks per pass through the stage buffers
-    constexpr bool paired = EPI == EPI_SWIGLU || EPI == EPI_QKV;
-    constexpr int W = paired ? 16 : 8;
-    static_for<0, NPASS>([&](auto p_c) {
-      constexpr int PS = decltype(p_c)::value;
-      constexpr int NB = PS * PB + PB <= FM ? PB : FM - PS * PB;  // row blocks in this pass
-      __syncthreads();  // every wave's DMAs have landed and the buffers' last readers are done
-      static_for<0, NB>([&](auto i) {
-        static_for<0, CB>([&](auto c) {
-          static_for<0, 16>([&](auto r) {
-            constexpr int R = decltype(r)::value;
-            const int row = (int)decltype(i)::value * 32 + 8 * (R / 4) + 4 * (lane >> 5) + (R % 4);
-            T_[row * TN + (wave * CB + (int)decltype(c)::value) * 32 + (lane & 31)] =
-                acc[PS * PB + decltype(i)::value][decltype(c)::value][R];
-          });
-        });
-      });
-      __syncthreads();
-      constexpr int ITEMS = 32 * NB * (TN / W);
-      for (int it = tid; it < ITEMS; it += 64 * NW) {
-        const int row = it / (TN / W), col = (it % (TN / W)) * W;
-        const int m = m0 + PS * PB * 32 + row, nc = n0 + col;
-        if (m >= a.M || nc >= a.N) continue;  // N % 16 == 0: a group is wholly inside or outside
-        float v[W];
-#pragma unroll
-        for (int e = 0; e < W; e += 4) *(f32x4*)&v[e] = *(const f32x4*)&T_[row * TN + col + e];
-        if (S > 1) {
-          float* dst = a.partial + ((size_t)sp * a.M + m) * a.N + nc;
-#pragma unroll
-          for (int e = 0; e < W; e += 4) *(f32x4*)(dst + e) = *(const f32x4*)&v[e];
-        } else if constexpr (paired) {
-          epi_group16<bf16, EPI>(a, m, nc, v, v + 8);
-        } else {
-          epi_group8<bf16, EPI>(a, m, nc, v);
-        }
-      }
-    });
-  };
-  if (wave < 4)
-    body(std::integral_constant<int, DW>{});
-  else
-    body(std::integral_constant<int, 0>{});
-}
-
 // NW-wave variant for 161..384 rows: the tile is 32 FM rows (FM = 5 or 6) x 32 NW columns, each
 // wave owning one 32-column weight block over all FM row blocks, so no weight fragment is loaded
 // twice and two row tiles fill the GPU where 288 x 128 tiles leave part of it idle.  Activations go
@@ -987,37 +811,24 @@ static int splits_for(int tiles, int units) {
 }
 
 // The wide 288 x 256 tile where it takes less time than the 288 x 128 one, whole passes of 256
-// workgroups compared with a wide tile measured at 1.8 times a narrow one (about 132 against
-// 76 us at K = 4096): at 2264 rows gate/up takes 3 wide passes instead of 6 narrow ones, and
-// at 518 one instead of 2.  Where one pass of wide tiles over the first columns and narrow
-// tiles for the rest cost less than either alone (QKV at 2264 rows: 1 wide pass over 8192
-// columns and 1 narrow pass over 4096, against 3 narrow or 2 wide passes), the launch is split
-// there.  The output and down projections at 2264 rows stay narrow.  Unsplit only.
+// workgroups compared with a wide tile measured at 1.5 times a narrow one (108 against 75 us a
+// full pass at K = 4096): at 2264 rows gate/up takes 3 wide passes instead of 6 narrow ones
+// (345 against 434 us), and at 527 one instead of 2 (104 against 136).  Where one pass of wide tiles
+// over the first columns and narrow tiles for the rest cost less than either alone (QKV at 2264
+// rows: 1 wide pass over 8192 columns and 1 narrow pass over 4096, against 3 narrow or 2 wide
+// passes, 228 or 216 us), the launch is split there.  The output and down projections at 2264
+// rows, one narrow pass, stay narrow.  Unsplit only.
 // Returns 0 (narrow), 1 (wide) or the first narrow column of a split launch.
 static int wide_plan(int epi, const GemmArgs& a) {
   if (a.splits != 1 || a.col0 != 0 || epi == EPI_STORE_F32 || fm_for(a.M) != 9 || a.M <= 32 * 12) return 0;
   const int mb = (a.M + 31) / 32, nb = (a.N + 31) / 32, n_mt = (mb + 8) / 9;
   auto passes = [](long t) { return (t + 255) / 256; };
   const long cost_n = passes((long)n_mt * ((nb + 3) / 4)) * 10;
-  const long cost_w = passes((long)n_mt * ((nb + 7) / 8)) * 18;
+  const long cost_w = passes((long)n_mt * ((nb + 7) / 8)) * 15;
   const int wblocks = (256 / n_mt) * 8;  // column blocks of one pass of wide tiles
-  const long cost_h = wblocks > 0 && wblocks < nb ? 18 + passes((long)n_mt * ((nb - wblocks + 3) / 4)) * 10 : cost_w + 1;
+  const long cost_h = wblocks > 0 && wblocks < nb ? 15 + passes((long)n_mt * ((nb - wblocks + 3) / 4)) * 10 : cost_w + 1;
   if (cost_h < cost_w && cost_h < cost_n) return wblocks * 32;
   return cost_w < cost_n ? 1 : 0;
-}
-
-static hipError_t gemm32w_launch(int epi, const GemmArgs& a, hipStream_t s) {
-  const int mb = (a.M + 31) / 32, nb = (a.N + 31) / 32;
-  constexpr int FM = 9, NW = 8, CB = 1;
-  const dim3 grid(((mb + FM - 1) / FM) * ((nb + NW * CB - 1) / (NW * CB)) * a.splits), block(64 * NW);
-  switch (epi) {
-    case EPI_STORE: hipLaunchKernelGGL((gemm32w_kernel<FM, NW, CB, EPI_STORE>), grid, block, 0, s, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((gemm32w_kernel<FM, NW, CB, EPI_RESID>), grid, block, 0, s, a); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm32w_kernel<FM, NW, CB, EPI_SWIGLU>), grid, block, 0, s, a); break;
-    case EPI_QKV: hipLaunchKernelGGL((gemm32w_kernel<FM, NW, CB, EPI_QKV>), grid, block, 0, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
 }
 
 static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) {
@@ -1036,14 +847,14 @@ static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) 
     return reduce_launch<bf16>(epi, a, s);
   }
   if (const int plan = wide_plan(epi, a)) {
-    if (plan == 1) return gemm32w_launch(epi, a, s);
+    if (plan == 1) return launch_gemm_wide(epi, a, s);
     // columns [0, plan) on wide tiles, the rest on 288 x 128 tiles
     GemmArgs aw = a, an = a;
     aw.N = plan;
     an.N = a.N - plan;
     an.col0 = plan;
     an.B = (const bf16*)a.B + (size_t)(plan / 32) * a.bstride;
-    e = gemm32w_launch(epi, aw, s);
+    e = launch_gemm_wide(epi, aw, s);
     if (e != hipSuccess) return e;
     return gemm32_launch<9, true>(epi, an, s);
   }
