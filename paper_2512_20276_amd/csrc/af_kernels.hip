@@ -99,7 +99,12 @@ __global__ __launch_bounds__(NORM_THREADS) void rmsnorm_kernel(const T* __restri
 // a row's load and its store.  Lane l holds chunks l + 64 i, which are the chunks thread
 // 64 i + l of rmsnorm_kernel holds; its squares are summed, tree-reduced over the 64 lanes and
 // the eight partial sums added in the same order as there, so every output is bit-identical.
+// Fragment-tiled output (FRAG) puts the same 8 k of eight consecutive rows side by side, 128 bytes:
+// written row by row, every store of 16 bytes went to a line of its own.  The rows meet in LDS
+// instead and every line is written whole (2264 x 4096: 18.4 -> 11.8 us).  Chunk c of row w sits at
+// os[w][c ^ w], so that neither the row-wise writes nor the line-wise reads meet on a bank.
 constexpr int NORM_ROWS_PER_WG = 8;
+template <bool FRAG>
 __global__ __launch_bounds__(64 * NORM_ROWS_PER_WG) void rmsnorm_rows_kernel(const bf16* __restrict__ x, int ldx,
                                                                        const int32_t* rows,
                                                                        const bf16* __restrict__ g, bf16* __restrict__ y,
@@ -108,6 +113,7 @@ __global__ __launch_bounds__(64 * NORM_ROWS_PER_WG) void rmsnorm_rows_kernel(con
   constexpr int CPL = NORM_THREADS / 64;  // chunks per lane: 4096 / 8 / 64
   static_assert(NORM_THREADS == 64 * NORM_ROWS_PER_WG, "one thread of rmsnorm_kernel per chunk");
   __shared__ __attribute__((aligned(16))) bf16 gs[NORM_THREADS * 8];
+  __shared__ uint4 os[FRAG ? NORM_ROWS_PER_WG : 1][FRAG ? NORM_THREADS : 1];
   const int lane = threadIdx.x & 63, r = blockIdx.x * NORM_ROWS_PER_WG + (threadIdx.x >> 6);
   const int n_chunks = D / 8;
   if ((int)threadIdx.x < n_chunks) *(uint4*)&gs[8 * threadIdx.x] = *(const uint4*)(g + 8 * threadIdx.x);
@@ -129,17 +135,27 @@ __global__ __launch_bounds__(64 * NORM_ROWS_PER_WG) void rmsnorm_rows_kernel(con
   }
   const float inv = 1.0f / sqrtf(tot / (float)D + eps);
   __syncthreads();  // the gain is in LDS
-  if (r >= n_rows) return;
 #pragma unroll
   for (int i = 0; i < CPL; ++i) {
     const int c = 64 * i + lane;
-    if (c >= n_chunks) continue;
+    if (c >= n_chunks || r >= n_rows) continue;
     bf16 gv[8], o[8];
     *(uint4*)gv = *(const uint4*)&gs[8 * c];
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = from_f<bf16>(to_f(v[i][e]) * inv * to_f(gv[e]));
-    bf16* dst = ystride > 0 ? y + frag_off(r, 8 * c, ystride) : y + (size_t)r * ldy + 8 * c;
-    *(uint4*)dst = *(const uint4*)o;
+    if constexpr (FRAG) {
+      const int w = threadIdx.x >> 6;
+      os[w][c ^ w] = *(const uint4*)o;
+    } else {
+      *(uint4*)(y + (size_t)r * ldy + 8 * c) = *(const uint4*)o;
+    }
+  }
+  if constexpr (FRAG) {
+    __syncthreads();
+    const int w = threadIdx.x & 7, m = blockIdx.x * NORM_ROWS_PER_WG + w;
+    if (m >= n_rows) return;
+    for (int c = threadIdx.x >> 3; c < n_chunks; c += NORM_THREADS / 8)
+      *(uint4*)(y + frag_off(m, 8 * c, ystride)) = os[w][c ^ w];
   }
 }
 
@@ -151,9 +167,13 @@ hipError_t launch_rmsnorm(int dtype, const void* x, int ldx, const int32_t* rows
                           long ystride, int n_rows, int D, float eps, hipStream_t s) {
   if (n_rows <= 0) return hipSuccess;
   if (dtype == AF_BF16 && n_rows >= NORM_ROWS_MIN && D % 8 == 0 && D <= 8 * NORM_THREADS && ldx % 8 == 0) {
-    hipLaunchKernelGGL(rmsnorm_rows_kernel, dim3((n_rows + NORM_ROWS_PER_WG - 1) / NORM_ROWS_PER_WG),
-                       dim3(64 * NORM_ROWS_PER_WG), 0, s, (const bf16*)x, ldx, rows, (const bf16*)g, (bf16*)y, ldy,
-                       ystride, n_rows, D, eps);
+    const dim3 grid((n_rows + NORM_ROWS_PER_WG - 1) / NORM_ROWS_PER_WG), block(64 * NORM_ROWS_PER_WG);
+    if (ystride > 0)
+      hipLaunchKernelGGL(rmsnorm_rows_kernel<true>, grid, block, 0, s, (const bf16*)x, ldx, rows, (const bf16*)g,
+                         (bf16*)y, ldy, ystride, n_rows, D, eps);
+    else
+      hipLaunchKernelGGL(rmsnorm_rows_kernel<false>, grid, block, 0, s, (const bf16*)x, ldx, rows, (const bf16*)g,
+                         (bf16*)y, ldy, ystride, n_rows, D, eps);
     return hipGetLastError();
   }
   if (dtype == AF_BF16)
