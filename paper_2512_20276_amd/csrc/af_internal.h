@@ -85,7 +85,6 @@ struct AttnArgs {
 
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs& a, hipStream_t s);
 hipError_t launch_attention(int dtype, int head_dim, const AttnArgs& a, int n_tiles, hipStream_t s);
-// y row-major (row stride ldy) or, when ystride > 0, fragment-tiled.
 // bf16 GEMM with the K range split over a workgroup's waves, for up to STREAM_MAX_M rows.
 constexpr int STREAM_MAX_M = 192;
 struct StreamPlan {
@@ -98,8 +97,21 @@ hipError_t launch_gemm_wide(int epi, const GemmArgs& a, hipStream_t s);
 // fp32 GEMM on 16 x 32 tiles, where gemm_f32_small says so (unsplit).
 bool gemm_f32_small(int M, int N);
 hipError_t launch_gemm_f32_small(int epi, const GemmArgs& a, hipStream_t s);
+// The step tables on their way to the device: n16 chunks of 16 bytes from pinned host memory, read
+// by extra workgroups of the call's first kernel (a copy command of its own takes 4 us, longer
+// than that kernel needs beside its own work).  n16 = 0: nothing to copy.
+struct DescCopy {
+  const void* src = nullptr;
+  void* dst = nullptr;
+  int n16 = 0;
+};
+__host__ __device__ inline int desc_blocks(const DescCopy& dc) {  // four chunks for a thread of 256, at most 8 blocks
+  const int b = (dc.n16 + 1023) / 1024;
+  return b < 8 ? b : 8;
+}
+// y row-major (row stride ldy) or, when ystride > 0, fragment-tiled.
 hipError_t launch_rmsnorm(int dtype, const void* x, int ldx, const int32_t* rows, const void* g, void* y, int ldy,
-                          long ystride, int n_rows, int D, float eps, hipStream_t s);
+                          long ystride, int n_rows, int D, float eps, hipStream_t s, const DescCopy& dc = {});
 // Residual update from split-K partial sums followed by the RMSNorm of the updated rows:
 // x[m] <- x[m] + sum_s partial[s][m] (rounded as the residual epilogue rounds), then y[m] =
 // RMSNorm(x[m]) * g exactly as launch_rmsnorm computes it.  partial is [splits][M][D].
@@ -110,7 +122,7 @@ hipError_t launch_resid_norm(int dtype, const float* partial, int splits, void* 
 hipError_t launch_to_frag(int dtype, const void* x, int ld, int M, int K, int Kp, void* y, long astride,
                           hipStream_t s);
 hipError_t launch_embed(int dtype, const int32_t* ids, const void* table, int vocab, const void* embeds, void* out,
-                        int M, int D, int32_t* err_count, hipStream_t s);
+                        int M, int D, int32_t* err_count, hipStream_t s, const DescCopy& dc = {});
 hipError_t launch_argmax(const float* logits, int n_rows, int V, int32_t* tokens, hipStream_t s);
 // Zero-fills n_runs runs of run_bytes (16-byte multiple, 16-byte aligned), run r at base + r * stride.
 hipError_t launch_zero_runs(void* base, int n_runs, size_t stride, size_t run_bytes, hipStream_t s);

@@ -5,6 +5,13 @@
 
 namespace af {
 
+// ------------------------------------------------------------------ step tables
+// Copies this workgroup's share of the step tables; workgroup `b` of desc_blocks(dc).
+__device__ __forceinline__ void desc_copy(const DescCopy& dc, int b) {
+  const int nb = desc_blocks(dc), nt = blockDim.x;
+  for (int i = b * nt + threadIdx.x; i < dc.n16; i += nb * nt) ((uint4*)dc.dst)[i] = ((const uint4*)dc.src)[i];
+}
+
 // ------------------------------------------------------------------ RMSNorm
 // One workgroup of NORM_THREADS threads per output row (a 4096-wide bf16 row is one 16-byte
 // chunk per thread: one memory latency); rows[] optionally selects the input row.  The
@@ -29,9 +36,13 @@ __device__ __forceinline__ float norm_block_sum(float v, float* red) {
 template <typename T>
 __global__ __launch_bounds__(NORM_THREADS) void rmsnorm_kernel(const T* __restrict__ x, int ldx, const int32_t* rows,
                                                       const T* __restrict__ g, T* __restrict__ y, int ldy,
-                                                      long ystride, int D, float eps) {
+                                                      long ystride, int n_rows, int D, float eps, DescCopy dc) {
   __shared__ float red[NORM_THREADS / 64];
   const int r_out = blockIdx.x;
+  if (r_out >= n_rows) {
+    desc_copy(dc, r_out - n_rows);
+    return;
+  }
   const int r_in = rows ? rows[r_out] : r_out;
   const T* xr = x + (size_t)r_in * ldx;
   constexpr int V = 16 / sizeof(T);
@@ -109,7 +120,11 @@ __global__ __launch_bounds__(64 * NORM_ROWS_PER_WG) void rmsnorm_rows_kernel(con
                                                                        const int32_t* rows,
                                                                        const bf16* __restrict__ g, bf16* __restrict__ y,
                                                                        int ldy, long ystride, int n_rows, int D,
-                                                                       float eps) {
+                                                                       float eps, DescCopy dc) {
+  if ((int)blockIdx.x * NORM_ROWS_PER_WG >= n_rows) {
+    desc_copy(dc, blockIdx.x - (n_rows + NORM_ROWS_PER_WG - 1) / NORM_ROWS_PER_WG);
+    return;
+  }
   constexpr int CPL = NORM_THREADS / 64;  // chunks per lane: 4096 / 8 / 64
   static_assert(NORM_THREADS == 64 * NORM_ROWS_PER_WG, "one thread of rmsnorm_kernel per chunk");
   __shared__ __attribute__((aligned(16))) bf16 gs[NORM_THREADS * 8];
@@ -164,24 +179,25 @@ __global__ __launch_bounds__(64 * NORM_ROWS_PER_WG) void rmsnorm_rows_kernel(con
 constexpr int NORM_ROWS_MIN = 1024;
 
 hipError_t launch_rmsnorm(int dtype, const void* x, int ldx, const int32_t* rows, const void* g, void* y, int ldy,
-                          long ystride, int n_rows, int D, float eps, hipStream_t s) {
+                          long ystride, int n_rows, int D, float eps, hipStream_t s, const DescCopy& dc) {
   if (n_rows <= 0) return hipSuccess;
+  const int nd = desc_blocks(dc);
   if (dtype == AF_BF16 && n_rows >= NORM_ROWS_MIN && D % 8 == 0 && D <= 8 * NORM_THREADS && ldx % 8 == 0) {
-    const dim3 grid((n_rows + NORM_ROWS_PER_WG - 1) / NORM_ROWS_PER_WG), block(64 * NORM_ROWS_PER_WG);
+    const dim3 grid((n_rows + NORM_ROWS_PER_WG - 1) / NORM_ROWS_PER_WG + nd), block(64 * NORM_ROWS_PER_WG);
     if (ystride > 0)
       hipLaunchKernelGGL(rmsnorm_rows_kernel<true>, grid, block, 0, s, (const bf16*)x, ldx, rows, (const bf16*)g,
-                         (bf16*)y, ldy, ystride, n_rows, D, eps);
+                         (bf16*)y, ldy, ystride, n_rows, D, eps, dc);
     else
       hipLaunchKernelGGL(rmsnorm_rows_kernel<false>, grid, block, 0, s, (const bf16*)x, ldx, rows, (const bf16*)g,
-                         (bf16*)y, ldy, ystride, n_rows, D, eps);
+                         (bf16*)y, ldy, ystride, n_rows, D, eps, dc);
     return hipGetLastError();
   }
   if (dtype == AF_BF16)
-    hipLaunchKernelGGL(rmsnorm_kernel<bf16>, dim3(n_rows), dim3(NORM_THREADS), 0, s, (const bf16*)x, ldx, rows,
-                       (const bf16*)g, (bf16*)y, ldy, ystride, D, eps);
+    hipLaunchKernelGGL(rmsnorm_kernel<bf16>, dim3(n_rows + nd), dim3(NORM_THREADS), 0, s, (const bf16*)x, ldx, rows,
+                       (const bf16*)g, (bf16*)y, ldy, ystride, n_rows, D, eps, dc);
   else
-    hipLaunchKernelGGL(rmsnorm_kernel<float>, dim3(n_rows), dim3(NORM_THREADS), 0, s, (const float*)x, ldx, rows,
-                       (const float*)g, (float*)y, ldy, ystride, D, eps);
+    hipLaunchKernelGGL(rmsnorm_kernel<float>, dim3(n_rows + nd), dim3(NORM_THREADS), 0, s, (const float*)x, ldx, rows,
+                       (const float*)g, (float*)y, ldy, ystride, n_rows, D, eps, dc);
   return hipGetLastError();
 }
 
@@ -349,8 +365,12 @@ hipError_t launch_to_frag(int dtype, const void* x, int ld, int M, int K, int Kp
 template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ ids, const T* __restrict__ table,
                                                     int vocab, const T* __restrict__ embeds, T* __restrict__ out,
-                                                    int D, int32_t* err_count) {
+                                                    int M, int D, int32_t* err_count, DescCopy dc) {
   const int m = blockIdx.x;
+  if (m >= M) {
+    desc_copy(dc, m - M);
+    return;
+  }
   const int id = ids[m];
   const T* src = nullptr;
   if (id >= 0 && id < vocab) src = table + (size_t)id * D;
@@ -366,14 +386,15 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
 }
 
 hipError_t launch_embed(int dtype, const int32_t* ids, const void* table, int vocab, const void* embeds, void* out,
-                        int M, int D, int32_t* err_count, hipStream_t s) {
+                        int M, int D, int32_t* err_count, hipStream_t s, const DescCopy& dc) {
   if (M <= 0) return hipSuccess;
+  const dim3 grid(M + desc_blocks(dc));
   if (dtype == AF_BF16)
-    hipLaunchKernelGGL(embed_kernel<bf16>, dim3(M), dim3(256), 0, s, ids, (const bf16*)table, vocab,
-                       (const bf16*)embeds, (bf16*)out, D, err_count);
+    hipLaunchKernelGGL(embed_kernel<bf16>, grid, dim3(256), 0, s, ids, (const bf16*)table, vocab,
+                       (const bf16*)embeds, (bf16*)out, M, D, err_count, dc);
   else
-    hipLaunchKernelGGL(embed_kernel<float>, dim3(M), dim3(256), 0, s, ids, (const float*)table, vocab,
-                       (const float*)embeds, (float*)out, D, err_count);
+    hipLaunchKernelGGL(embed_kernel<float>, grid, dim3(256), 0, s, ids, (const float*)table, vocab,
+                       (const float*)embeds, (float*)out, M, D, err_count, dc);
   return hipGetLastError();
 }
 

@@ -91,7 +91,9 @@ struct Ws {
   af_weights* timing = nullptr;
   void *xn = nullptr, *q = nullptr, *attn = nullptr, *act = nullptr, *emit_norm = nullptr;
   float* logits = nullptr;  // fp32 logits of the emitting rows when the caller passes none
-  int32_t* desc = nullptr;  // the uploaded step tables
+  int32_t* desc = nullptr;  // the step tables on the device
+  DescCopy dc;              // how they get there with the call's first kernel (n16 = 0: they are there)
+  StageBuf* staged = nullptr;  // the pinned buffer that kernel reads
   const float* rope = nullptr;
   float* partial = nullptr;
   size_t partial_cap = 0;   // floats
@@ -265,10 +267,11 @@ void build_desc(const af_segment* segs, int n_seg, int M, StepDesc& sd) {
   }
 }
 
-// Uploads the descriptor through a rotating set of pinned staging buffers.  Calls on one
-// weights object are expected on one stream (the device copy of the descriptor is reused).
-af_status upload_desc(af_weights* w, const StepDesc& sd, hipStream_t s) {
-  const size_t n = sd.buf.size();
+// Puts the descriptor into one of a rotating set of pinned staging buffers, which the call's first
+// kernel reads (see DescCopy); staged_done() then marks the buffer as in use until that kernel
+// ends.  Calls on one weights object are expected on one stream (the device copy is reused).
+af_status stage_desc(af_weights* w, const StepDesc& sd, StageBuf** out) {
+  const size_t n = (sd.buf.size() + 3) / 4 * 4;  // whole 16-byte chunks
   if (n > w->desc_cap) {
     if (w->desc_dev) {
       AF_HIP(hipDeviceSynchronize());
@@ -298,11 +301,25 @@ af_status upload_desc(af_weights* w, const StepDesc& sd, hipStream_t s) {
     }
     sb.cap = cap;
   }
-  std::memcpy(sb.host, sd.buf.data(), n * 4);
-  AF_HIP(hipMemcpyAsync(w->desc_dev, sb.host, n * 4, hipMemcpyHostToDevice, s));
-  AF_HIP(hipEventRecord(sb.done, s));
-  sb.pending = true;
+  std::memcpy(sb.host, sd.buf.data(), sd.buf.size() * 4);
+  *out = &sb;
   return AF_OK;
+}
+
+// The kernel that reads the staged tables has been launched on s.
+af_status staged_done(StageBuf* sb, hipStream_t s) {
+  if (!sb) return AF_OK;
+  AF_HIP(hipEventRecord(sb->done, s));
+  sb->pending = true;
+  return AF_OK;
+}
+
+// The tables as a copy of their own, for calls whose first kernel does not take them.
+af_status upload_desc(af_weights* w, const StepDesc& sd, hipStream_t s) {
+  StageBuf* sb = nullptr;
+  AF_TRY(stage_desc(w, sd, &sb));
+  AF_HIP(hipMemcpyAsync(w->desc_dev, sb->host, sd.buf.size() * 4, hipMemcpyHostToDevice, s));
+  return staged_done(sb, s);
 }
 
 // Bytes of a GEMM-input activation buffer for `rows` rows of width K (layout per dtype).
@@ -584,11 +601,19 @@ af_status step_down(af_weights* w, Ws& ws, int l, const void* act, int ld_act, l
 }
 
 af_status step_norm(af_weights* w, af_weights* tw, const void* x, int ldx, const int32_t* rows, const void* g,
-                    void* y, int ldy, long ys, int n_rows, hipStream_t s) {
+                    void* y, int ldy, long ys, int n_rows, hipStream_t s, const DescCopy& dc = {}) {
   const af_model_desc& d = w->d;
   return timed(tw, AF_K_RMSNORM, s, [&] {
-    return launch_rmsnorm(d.dtype, x, ldx, rows, g, y, ldy, ys, n_rows, d.d_model, d.rms_eps, s);
+    return launch_rmsnorm(d.dtype, x, ldx, rows, g, y, ldy, ys, n_rows, d.d_model, d.rms_eps, s, dc);
   });
+}
+
+// The call's first kernel has taken the step tables along.
+af_status tables_sent(Ws& ws, hipStream_t s) {
+  AF_TRY(staged_done(ws.staged, s));
+  ws.dc = DescCopy{};
+  ws.staged = nullptr;
+  return AF_OK;
 }
 
 // One decoder layer (Alg. 2).  xn_ready: the previous layer's down projection already wrote
@@ -601,7 +626,10 @@ af_status layer_forward(af_weights* w, Ws& ws, int l, void* hidden, int M, af_ri
   const Layer& L = w->layers[l];
   const int D = w->d.d_model, ldD = w->ldD, ldF = w->ldF;
   const long xD = w->xs_D, xF = w->xs_F;  // 0 (row-major) for fp32
-  if (!xn_ready) AF_TRY(step_norm(w, ws.timing, hidden, D, nullptr, L.attn_norm, ws.xn, ldD, xD, M, s));
+  if (!xn_ready) {
+    AF_TRY(step_norm(w, ws.timing, hidden, D, nullptr, L.attn_norm, ws.xn, ldD, xD, M, s, ws.dc));
+    AF_TRY(tables_sent(ws, s));
+  }
   AF_TRY(step_qkv(w, ws, l, ws.xn, ldD, xD, M, ring, rl, t, ws.q, ldD, s));
   AF_TRY(step_attention(ws.timing, w->d.dtype, ring, rl, ws.q, ldD, ws.attn, ldD, xD, t, s));
   // InPlaceKVShift: no device work; the slot rotation lives in the ring bookkeeping.
@@ -620,6 +648,7 @@ af_status lm_head(af_weights* w, Ws& ws, const void* hidden, const DevTables& t,
   if (t.n_emit == 0 || (!out_logits && !out_tokens)) return AF_OK;
   AF_TRY(step_norm(w, ws.timing, hidden, d.d_model, t.emit_rows, w->final_norm, ws.emit_norm, w->ldD, w->xs_D,
                    t.n_emit, s));
+  AF_TRY(tables_sent(ws, s));
   float* logits = out_logits ? out_logits : ws.logits;
   GemmArgs g = gemm_args(d.dtype, ws.emit_norm, w->ldD, w->xs_D, w->lm_head, t.n_emit, d.vocab, d.d_model, logits,
                          d.vocab);
@@ -631,13 +660,24 @@ af_status lm_head(af_weights* w, Ws& ws, const void* hidden, const DevTables& t,
 }
 
 af_status prepare_step(af_weights* w, af_ring* ring, const af_segment* segs, int n_seg, int M, int min_layers,
-                       StepDesc& sd, hipStream_t s) {
+                       StepDesc& sd) {
   AF_TRY(check_ring_matches(w, ring, min_layers));
   AF_TRY(check_segments(ring, segs, n_seg, M));
   build_desc(segs, n_seg, M, sd);
   AF_TRY(ensure_workspace(w, M, sd.n_emit));
   AF_TRY(ensure_rope(w, ring->d.max_pos));
-  AF_TRY(upload_desc(w, sd, s));
+  return AF_OK;
+}
+
+// The workspace of a call whose first kernel (embedding or norm) takes the step tables along.
+af_status ws_with_tables(af_weights* w, const StepDesc& sd, Ws* ws) {
+  StageBuf* sb = nullptr;
+  AF_TRY(stage_desc(w, sd, &sb));
+  *ws = ws_of(w);
+  ws->dc.src = sb->host;
+  ws->dc.dst = ws->desc;
+  ws->dc.n16 = (int)((sd.buf.size() + 3) / 4);
+  ws->staged = sb;
   return AF_OK;
 }
 
@@ -647,8 +687,9 @@ af_status forward_steps(af_weights* w, Ws& ws, const DevTables& t, const int32_t
                         hipStream_t s) {
   const af_model_desc& d = w->d;
   AF_TRY(timed(ws.timing, AF_K_EMBED, s, [&] {
-    return launch_embed(d.dtype, token_ids, w->embed, d.vocab, embeds, out_hidden, M, d.d_model, w->dev_err, s);
+    return launch_embed(d.dtype, token_ids, w->embed, d.vocab, embeds, out_hidden, M, d.d_model, w->dev_err, s, ws.dc);
   }));
+  AF_TRY(tables_sent(ws, s));
   bool xn_ready = false;
   for (int l = 0; l < d.n_layers; ++l) {
     const void* next = l + 1 < d.n_layers ? w->layers[l + 1].attn_norm : nullptr;
@@ -841,8 +882,9 @@ extern "C" af_status af_packed_forward(af_weights* w, const int32_t* token_ids, 
   AF_TRY(check_forward_args(w, token_ids, out_hidden, ring));
   hipStream_t s = (hipStream_t)hip_stream;
   StepDesc sd;
-  AF_TRY(prepare_step(w, ring, segs, n_seg, M, w->d.n_layers, sd, s));
-  Ws ws = ws_of(w);
+  AF_TRY(prepare_step(w, ring, segs, n_seg, M, w->d.n_layers, sd));
+  Ws ws;
+  AF_TRY(ws_with_tables(w, sd, &ws));
   return forward_steps(w, ws, dev_tables(ws.desc, sd), token_ids, embeds, M, ring, out_hidden, out_logits,
                        out_tokens, s);
 }
@@ -871,8 +913,9 @@ extern "C" af_status af_packed_layer_forward_kv(af_weights* w, int32_t layer, vo
   }
   hipStream_t s = (hipStream_t)hip_stream;
   StepDesc sd;
-  AF_TRY(prepare_step(w, ring, segs, n_seg, M, ring_layer + 1, sd, s));
-  Ws ws = ws_of(w);
+  AF_TRY(prepare_step(w, ring, segs, n_seg, M, ring_layer + 1, sd));
+  Ws ws;
+  AF_TRY(ws_with_tables(w, sd, &ws));
   return layer_forward(w, ws, layer, hidden_inout, M, ring, ring_layer, dev_tables(ws.desc, sd), s);
 }
 
@@ -1061,7 +1104,8 @@ extern "C" af_status af_op_qkv_rope_write(af_weights* w, int32_t layer, const vo
   }
   hipStream_t s = (hipStream_t)hip_stream;
   StepDesc sd;
-  AF_TRY(prepare_step(w, ring, segs, n_seg, M, layer + 1, sd, s));
+  AF_TRY(prepare_step(w, ring, segs, n_seg, M, layer + 1, sd));
+  AF_TRY(upload_desc(w, sd, s));
   AF_TRY(stage_input(w, xn, w->d.d_model, M, w->xn, w->xs_D, s));
   Ws ws = ws_of(w);
   return step_qkv(w, ws, layer, xn, w->d.d_model, w->xs_D, M, ring, layer, dev_tables(ws.desc, sd), q_out,
@@ -1163,9 +1207,10 @@ extern "C" af_status af_op_lm_head_argmax(af_weights* w, const void* hidden, int
   StepDesc sd;
   build_desc(segs, n_seg, M, sd);
   AF_TRY(ensure_workspace(w, M, sd.n_emit));
-  AF_TRY(upload_desc(w, sd, s));
-  Ws ws = ws_of(w);
-  return lm_head(w, ws, hidden, dev_tables(ws.desc, sd), out_logits, out_tokens, s);
+  // only the norm reads a table (its row list): it reads the pinned buffer itself
+  Ws ws;
+  AF_TRY(ws_with_tables(w, sd, &ws));
+  return lm_head(w, ws, hidden, dev_tables((const int32_t*)ws.dc.src, sd), out_logits, out_tokens, s);
 }
 
 extern "C" af_status af_weights_set_options(af_weights* w, uint32_t flags) {
