@@ -831,6 +831,13 @@ static int wide_plan(int epi, const GemmArgs& a) {
   return cost_w < cost_n ? 1 : 0;
 }
 
+// 288 x 128 tiles: with two k groups of waves, or in the one order of summation that every other
+// tile shape shares (and for the fp32 store, which no path takes at this many rows).
+static hipError_t gemm_launch_9(int epi, const GemmArgs& a, hipStream_t s) {
+  if (!a.fixed_order && epi != EPI_STORE_F32) return launch_gemm_ksplit(epi, a, s);
+  return gemm32_launch<9, true>(epi, a, s);
+}
+
 static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) {
   if (a.astride <= 0 || a.Kp % 256 != 0 || a.astride < (long)a.Kp * 32 || a.bstride < (long)a.Kp * 32)
     return hipErrorInvalidValue;
@@ -856,14 +863,14 @@ static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) 
     an.B = (const bf16*)a.B + (size_t)(plan / 32) * a.bstride;
     e = launch_gemm_wide(epi, aw, s);
     if (e != hipSuccess) return e;
-    return gemm32_launch<9, true>(epi, an, s);
+    return gemm_launch_9(epi, an, s);
   }
   switch (fm_for(a.M)) {
     case 1: e = gemm32_launch<1, false>(epi, a, s); break;
     case 3: e = gemm32_launch<3, true>(epi, a, s); break;
     case 5: e = gemm32_launch<5, true>(epi, a, s); break;
     case 7: e = gemm32_launch<7, true>(epi, a, s); break;
-    case 9: e = gemm32_launch<9, true>(epi, a, s); break;
+    case 9: e = gemm_launch_9(epi, a, s); break;
     default: e = gemm32_launch<10, true>(epi, a, s); break;
   }
   if (e != hipSuccess || a.splits <= 1 || a.partials_only) return e;

@@ -92,8 +92,10 @@ struct StreamPlan {
 };
 bool stream_plan(int M, int N, int Kp, int epi, StreamPlan* p);
 hipError_t launch_gemm_stream(const StreamPlan& p, int epi, const GemmArgs& a, hipStream_t s);
-// bf16 GEMM on 288 x 256 tiles (unsplit; not EPI_STORE_F32).
+// bf16 GEMM on 288 x 256 tiles, and on 288 x 128 tiles with two k groups (not with fixed_order); with
+// splits > 1 partial sums only.  Neither takes EPI_STORE_F32.
 hipError_t launch_gemm_wide(int epi, const GemmArgs& a, hipStream_t s);
+hipError_t launch_gemm_ksplit(int epi, const GemmArgs& a, hipStream_t s);
 // fp32 GEMM on 16 x 32 tiles, where gemm_f32_small says so (unsplit).
 bool gemm_f32_small(int M, int N);
 hipError_t launch_gemm_f32_small(int epi, const GemmArgs& a, hipStream_t s);

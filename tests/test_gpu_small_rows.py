@@ -1,8 +1,8 @@
-"""GPU parity of the projection GEMMs for few rows at the edges of their tiles.
+"""GPU parity of the projection GEMMs at the edges of their tiles.
 
 bf16 up to 192 rows runs with K split over a workgroup's waves (one kernel instance per number of
 32-row blocks, tiles of 1 to 4 column blocks, 1 to 8 K splits); fp32 projections of up to 1024
-tiles of 16 x 32 run on those.  Every element is held to what its arithmetic allows: fp32 sums of
+tiles of 16 x 32 run on those; bf16 tiles of 288 rows split k between two groups of waves.  Every element is held to what its arithmetic allows: fp32 sums of
 K products in any order lie within K 2^-24 sum |x w| of the exact value, and storing in bf16 adds
 at most 2^-8 of it.
 """
@@ -44,6 +44,14 @@ def test_bf16_row_block_edges(M, N, K):
 def test_bf16_projection_widths(M, N, K):
     """The 7B projections' widths with their K splits (11008: shares of 43 k units), and widths
     that take three and four column blocks per tile."""
+    _check(M, N, K, torch.bfloat16)
+
+
+@pytest.mark.parametrize("M", [257, 288, 385, 543, 576, 577, 2264])
+@pytest.mark.parametrize("N,K", [(48, 256), (608, 1024), (4096, 512)])
+def test_bf16_two_k_groups(M, N, K):
+    """288 x 128 tiles with two k groups: row tiles of one row and of 288, a last column block
+    half past N, a last column tile partly past it, K split over workgroups (48, 608) and not."""
     _check(M, N, K, torch.bfloat16)
 
 
