@@ -29,9 +29,12 @@ struct Layer {
 // K of the fragment-tiled weights: padded so the GEMM's k loop has no partial unrolled block.
 inline int padk(int k) { return (k + gemm_k_align() - 1) / gemm_k_align() * gemm_k_align(); }
 
-struct StageBuf {  // pinned staging for one descriptor upload
-  int32_t* host = nullptr;
-  size_t cap = 0;  // int32 elements
+// Pinned staging of step tables: STAGE_GROUPS groups of STAGE_PER_GROUP buffers, used in turn.  An
+// event behind a group's last reader guards the whole group (the calls of one weights object are
+// ordered).  One event a group, since an event between two kernels keeps the second waiting: 5.7 us
+// of the stream when every call recorded one.
+constexpr int STAGE_GROUPS = 4, STAGE_PER_GROUP = 8;
+struct StageGroup {
   hipEvent_t done = nullptr;
   bool pending = false;
 };
@@ -71,8 +74,9 @@ struct af_weights {
 
   int32_t* desc_dev = nullptr;
   size_t desc_cap = 0;
-  StageBuf stage[4];
-  int stage_next = 0;
+  int32_t* stage_host = nullptr;  // one buffer of desc_cap words per staged call
+  StageGroup stage[STAGE_GROUPS];
+  int stage_next = 0;             // the buffer of the next call
 
   uint32_t options = 0;
   uint32_t timing_mask = 0;
@@ -93,7 +97,7 @@ struct Ws {
   float* logits = nullptr;  // fp32 logits of the emitting rows when the caller passes none
   int32_t* desc = nullptr;  // the step tables on the device
   DescCopy dc;              // how they get there with the call's first kernel (n16 = 0: they are there)
-  StageBuf* staged = nullptr;  // the pinned buffer that kernel reads
+  bool staged = false;      // that kernel reads the next staging buffer
   const float* rope = nullptr;
   float* partial = nullptr;
   size_t partial_cap = 0;   // floats
@@ -267,59 +271,63 @@ void build_desc(const af_segment* segs, int n_seg, int M, StepDesc& sd) {
   }
 }
 
-// Puts the descriptor into one of a rotating set of pinned staging buffers, which the call's first
-// kernel reads (see DescCopy); staged_done() then marks the buffer as in use until that kernel
-// ends.  Calls on one weights object are expected on one stream (the device copy is reused).
-af_status stage_desc(af_weights* w, const StepDesc& sd, StageBuf** out) {
+// Puts the descriptor into the next pinned staging buffer, which the call's first kernel reads (see
+// DescCopy); staged_done() then keeps the buffer until that kernel ends.  Calls on one weights
+// object are expected on one stream, or ordered (the device copy is reused).
+af_status stage_desc(af_weights* w, const StepDesc& sd, int32_t** out) {
   const size_t n = (sd.buf.size() + 3) / 4 * 4;  // whole 16-byte chunks
   if (n > w->desc_cap) {
     if (w->desc_dev) {
       AF_HIP(hipDeviceSynchronize());
+      for (StageGroup& g : w->stage) g.pending = false;
+      if (w->stage_host) (void)hipHostFree(w->stage_host);
+      w->stage_host = nullptr;
+      w->desc_cap = 0;
       dev_free(w, w->desc_dev);
       w->desc_dev = nullptr;
     }
-    size_t cap = std::max<size_t>(n, 4096);
+    size_t cap = 4096;
+    while (cap < n) cap *= 2;
     AF_TRY(dev_alloc(w, (void**)&w->desc_dev, cap * 4));
-    w->desc_cap = cap;
-  }
-  StageBuf& sb = w->stage[w->stage_next];
-  w->stage_next = (w->stage_next + 1) % 4;
-  if (sb.pending) {
-    AF_HIP(hipEventSynchronize(sb.done));
-    sb.pending = false;
-  }
-  if (!sb.done) AF_HIP(hipEventCreateWithFlags(&sb.done, hipEventDisableTiming));
-  if (n > sb.cap) {
-    if (sb.host) (void)hipHostFree(sb.host);
-    sb.host = nullptr;
-    size_t cap = std::max<size_t>(n, 4096);
-    hipError_t e = hipHostMalloc((void**)&sb.host, cap * 4, hipHostMallocDefault);
+    // coherent: a buffer's later contents are read by later kernels with no event in between
+    const size_t bytes = cap * 4 * STAGE_GROUPS * STAGE_PER_GROUP;
+    hipError_t e = hipHostMalloc((void**)&w->stage_host, bytes, hipHostMallocCoherent);
     if (e != hipSuccess) {
-      sb.cap = 0;
-      set_error("hipHostMalloc(%zu) failed: %s", cap * 4, hipGetErrorString(e));
+      w->stage_host = nullptr;
+      set_error("hipHostMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
       return AF_ERR_OOM;
     }
-    sb.cap = cap;
+    w->desc_cap = cap;
   }
-  std::memcpy(sb.host, sd.buf.data(), sd.buf.size() * 4);
-  *out = &sb;
+  StageGroup& g = w->stage[w->stage_next / STAGE_PER_GROUP];
+  if (g.pending) {
+    AF_HIP(hipEventSynchronize(g.done));
+    g.pending = false;
+  }
+  if (!g.done) AF_HIP(hipEventCreateWithFlags(&g.done, hipEventDisableTiming));
+  *out = w->stage_host + (size_t)w->stage_next * w->desc_cap;
+  std::memcpy(*out, sd.buf.data(), sd.buf.size() * 4);
   return AF_OK;
 }
 
-// The kernel that reads the staged tables has been launched on s.
-af_status staged_done(StageBuf* sb, hipStream_t s) {
-  if (!sb) return AF_OK;
-  AF_HIP(hipEventRecord(sb->done, s));
-  sb->pending = true;
+// The kernel that reads the staged tables has been launched on s: the next call takes the next
+// buffer.
+af_status staged_done(af_weights* w, hipStream_t s) {
+  const int i = w->stage_next;
+  w->stage_next = (i + 1) % (STAGE_GROUPS * STAGE_PER_GROUP);
+  if ((i + 1) % STAGE_PER_GROUP) return AF_OK;
+  StageGroup& g = w->stage[i / STAGE_PER_GROUP];
+  AF_HIP(hipEventRecord(g.done, s));
+  g.pending = true;
   return AF_OK;
 }
 
 // The tables as a copy of their own, for calls whose first kernel does not take them.
 af_status upload_desc(af_weights* w, const StepDesc& sd, hipStream_t s) {
-  StageBuf* sb = nullptr;
-  AF_TRY(stage_desc(w, sd, &sb));
-  AF_HIP(hipMemcpyAsync(w->desc_dev, sb->host, sd.buf.size() * 4, hipMemcpyHostToDevice, s));
-  return staged_done(sb, s);
+  int32_t* host = nullptr;
+  AF_TRY(stage_desc(w, sd, &host));
+  AF_HIP(hipMemcpyAsync(w->desc_dev, host, sd.buf.size() * 4, hipMemcpyHostToDevice, s));
+  return staged_done(w, s);
 }
 
 // Bytes of a GEMM-input activation buffer for `rows` rows of width K (layout per dtype).
@@ -609,11 +617,11 @@ af_status step_norm(af_weights* w, af_weights* tw, const void* x, int ldx, const
 }
 
 // The call's first kernel has taken the step tables along.
-af_status tables_sent(Ws& ws, hipStream_t s) {
-  AF_TRY(staged_done(ws.staged, s));
+af_status tables_sent(af_weights* w, Ws& ws, hipStream_t s) {
+  if (!ws.staged) return AF_OK;
   ws.dc = DescCopy{};
-  ws.staged = nullptr;
-  return AF_OK;
+  ws.staged = false;
+  return staged_done(w, s);
 }
 
 // One decoder layer (Alg. 2).  xn_ready: the previous layer's down projection already wrote
@@ -628,7 +636,7 @@ af_status layer_forward(af_weights* w, Ws& ws, int l, void* hidden, int M, af_ri
   const long xD = w->xs_D, xF = w->xs_F;  // 0 (row-major) for fp32
   if (!xn_ready) {
     AF_TRY(step_norm(w, ws.timing, hidden, D, nullptr, L.attn_norm, ws.xn, ldD, xD, M, s, ws.dc));
-    AF_TRY(tables_sent(ws, s));
+    AF_TRY(tables_sent(w, ws, s));
   }
   AF_TRY(step_qkv(w, ws, l, ws.xn, ldD, xD, M, ring, rl, t, ws.q, ldD, s));
   AF_TRY(step_attention(ws.timing, w->d.dtype, ring, rl, ws.q, ldD, ws.attn, ldD, xD, t, s));
@@ -648,7 +656,7 @@ af_status lm_head(af_weights* w, Ws& ws, const void* hidden, const DevTables& t,
   if (t.n_emit == 0 || (!out_logits && !out_tokens)) return AF_OK;
   AF_TRY(step_norm(w, ws.timing, hidden, d.d_model, t.emit_rows, w->final_norm, ws.emit_norm, w->ldD, w->xs_D,
                    t.n_emit, s));
-  AF_TRY(tables_sent(ws, s));
+  AF_TRY(tables_sent(w, ws, s));
   float* logits = out_logits ? out_logits : ws.logits;
   GemmArgs g = gemm_args(d.dtype, ws.emit_norm, w->ldD, w->xs_D, w->lm_head, t.n_emit, d.vocab, d.d_model, logits,
                          d.vocab);
@@ -671,13 +679,13 @@ af_status prepare_step(af_weights* w, af_ring* ring, const af_segment* segs, int
 
 // The workspace of a call whose first kernel (embedding or norm) takes the step tables along.
 af_status ws_with_tables(af_weights* w, const StepDesc& sd, Ws* ws) {
-  StageBuf* sb = nullptr;
-  AF_TRY(stage_desc(w, sd, &sb));
+  int32_t* host = nullptr;
+  AF_TRY(stage_desc(w, sd, &host));
   *ws = ws_of(w);
-  ws->dc.src = sb->host;
+  ws->dc.src = host;
   ws->dc.dst = ws->desc;
   ws->dc.n16 = (int)((sd.buf.size() + 3) / 4);
-  ws->staged = sb;
+  ws->staged = true;
   return AF_OK;
 }
 
@@ -689,7 +697,7 @@ af_status forward_steps(af_weights* w, Ws& ws, const DevTables& t, const int32_t
   AF_TRY(timed(ws.timing, AF_K_EMBED, s, [&] {
     return launch_embed(d.dtype, token_ids, w->embed, d.vocab, embeds, out_hidden, M, d.d_model, w->dev_err, s, ws.dc);
   }));
-  AF_TRY(tables_sent(ws, s));
+  AF_TRY(tables_sent(w, ws, s));
   bool xn_ready = false;
   for (int l = 0; l < d.n_layers; ++l) {
     const void* next = l + 1 < d.n_layers ? w->layers[l + 1].attn_norm : nullptr;
@@ -723,10 +731,9 @@ extern "C" af_status af_weights_destroy(af_weights* w) {
   if (!w) return AF_OK;
   (void)hipDeviceSynchronize();
   for (void* p : w->allocs) (void)hipFree(p);
-  for (auto& sb : w->stage) {
-    if (sb.host) (void)hipHostFree(sb.host);
-    if (sb.done) (void)hipEventDestroy(sb.done);
-  }
+  if (w->stage_host) (void)hipHostFree(w->stage_host);
+  for (StageGroup& g : w->stage)
+    if (g.done) (void)hipEventDestroy(g.done);
   for (auto& t : w->timed) {
     (void)hipEventDestroy(t.start);
     (void)hipEventDestroy(t.stop);

@@ -61,3 +61,44 @@ def test_f32_small_tiles(M, N, K):
     """Row and column remainders of the 16 x 32 tile; K below, at and past what a wave requests at
     once (two steps of 32 at K <= 256, six beyond, and more than one such share)."""
     _check(M, N, K, torch.float32)
+
+
+def test_step_tables_of_calls_in_flight():
+    """Calls whose tables differ, sent without waiting, twice round the staging buffers and with
+    tables that outgrow them on the way: every call reads its own tables."""
+    shape = wl.TINY
+    g, layers = wl.model_weights(shape, seed=3, device="cuda")
+    n_req, rows = 12, 2500
+    order = [[(5 * i + j) % n_req for j in range(1 + i % n_req)] for i in range(72)]
+
+    def all_calls(wait):
+        w = af.Weights(shape, g, layers)
+        ring = af.Ring(shape.n_layers, n_req + 1, 2560, shape.n_heads, shape.head_dim, dtype=torch.float32)
+        segs = {}
+        for r in range(n_req):
+            slot = ring.append(r, 3 + r).slot
+            kv = [wl.draw(("t_tab", n, r), (3 + r, shape.n_heads, shape.head_dim), dtype=torch.float32,
+                          device="cuda") for n in "kv"]
+            ring.write_kv(0, slot, 0, *kv)
+            segs[r] = ring.append(r, 1)
+        long = ring.append(n_req, rows)
+        out = []
+        for i, reqs in enumerate(order):
+            call = [segs[r] for r in reqs] if i != 40 else [long]
+            for row, s in enumerate(call):
+                s.q_start, s.flags = row, af.AF_SEG_EMIT
+            # a request's row is the same in every call, so are the keys and values it writes
+            ids = reqs if i != 40 else range(100, 100 + rows)
+            h = torch.stack([base[r] for r in ids])
+            af.packed_layer_forward(w, 0, h, af.segments_array(call), ring)
+            z = torch.empty((len(call), shape.vocab), dtype=torch.float32, device="cuda")
+            af.op_lm_head_argmax(w, h, af.segments_array(call), z)
+            if wait:
+                torch.cuda.synchronize()
+            out += [h, z]
+        torch.cuda.synchronize()
+        return out
+
+    base = wl.draw(("t_tab_x",), (100 + rows, shape.d_model), dtype=torch.float32, device="cuda")
+    for i, (a, b) in enumerate(zip(all_calls(True), all_calls(False))):
+        assert torch.equal(a, b), i
