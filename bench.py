@@ -96,6 +96,10 @@ def measured_traffic():
 def _kernel_class(name: str) -> str:
     """Maps a kernel name (mangled or demangled) to the label used in the summaries."""
     import re
+    if "gemm_stream_kernel" in name:  # its epilogue is an argument
+        return "gemm (up to 192 rows)"
+    if "gemm_f32_small_kernel" in name:
+        return "gemm (fp32, small model)"
     if any(k in name for k in ("gemm_kernel", "gemm32_kernel", "gemm32x2_kernel", "gemm32c_kernel",
                                "gemm32w_kernel")):
         epi = (re.search(r"gemm32(?:x2|c|w)?_kernelI(?:Li\d+E)*Li(\d+)EEEv", name)    # bf16, mangled
@@ -103,7 +107,7 @@ def _kernel_class(name: str) -> str:
                or re.search(r",\s*(\d)>\s*\(", name) or re.search(r",\s*\(af::Epi\)(\d)>", name)
                or re.search(r"GemmCfgI(?:Li\d+E)+EELi(\d)E", name))                  # fp32 kernel
         e = int(epi.group(1)) if epi else -1
-        if "gemm32c_kernel" in name and e == 0:  # its split-K instance: partial sums only
+        if ("gemm32c_kernel" in name or "gemm32w_kernel" in name) and e == 0:  # split-K: partial sums only
             return "gemm (split-K partials: QKV / O / down)"
         return {0: "gemm (store)", 1: "gemm (f32 store, LM head)", 2: "gemm (+residual: O / down)",
                 3: "gemm (gate/up + SwiGLU)", 4: "gemm (QKV + RoPE + ring write)"}.get(e, "gemm")
