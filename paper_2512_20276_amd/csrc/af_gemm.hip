@@ -838,12 +838,25 @@ static hipError_t gemm_launch_9(int epi, const GemmArgs& a, hipStream_t s) {
   return gemm32_launch<9, true>(epi, a, s);
 }
 
+// Split-K factor of the bf16 tiles of this file.
+static int tile_splits(int M, int N, int Kp) {
+  if (const int S = c6_narrow(M, N, Kp)) return S;
+  if (const int S = c6_wide_splits(M, N, Kp)) return S;
+  const int fm = fm_for(M);
+  const int tiles = (((M + 31) / 32 + fm - 1) / fm) * (((N + 31) / 32 + 3) / 4);
+  return splits_for(tiles, Kp / gemm_k_align());
+}
+// The streaming plan of a launch, if it takes that kernel.
+static bool stream_plan_for(int M, int N, int Kp, int epi, StreamPlan* p) {
+  return M <= STREAM_MAX_M && stream_plan(M, N, Kp, epi, tile_splits(M, N, Kp), p);
+}
+
 static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) {
   if (a.astride <= 0 || a.Kp % 256 != 0 || a.astride < (long)a.Kp * 32 || a.bstride < (long)a.Kp * 32)
     return hipErrorInvalidValue;
   hipError_t e;
   StreamPlan sp;
-  if (!a.fixed_order && stream_plan(a.M, a.N, a.Kp, epi, &sp) && sp.splits == a.splits) {
+  if (!a.fixed_order && stream_plan_for(a.M, a.N, a.Kp, epi, &sp) && sp.splits == a.splits) {
     e = launch_gemm_stream(sp, epi, a, s);
     if (e != hipSuccess || a.splits <= 1 || a.partials_only) return e;
     return reduce_launch<bf16>(epi, a, s);
@@ -880,12 +893,7 @@ static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) 
 int gemm_splits(int dtype, int epi, int M, int N, int Kp) {
   if (dtype == AF_BF16) {
     StreamPlan sp;
-    if (stream_plan(M, N, Kp, epi, &sp)) return sp.splits;
-    if (const int S = c6_narrow(M, N, Kp)) return S;
-    if (const int S = c6_wide_splits(M, N, Kp)) return S;
-    const int fm = fm_for(M);
-    const int tiles = (((M + 31) / 32 + fm - 1) / fm) * (((N + 31) / 32 + 3) / 4);
-    return splits_for(tiles, Kp / gemm_k_align());
+    return stream_plan_for(M, N, Kp, epi, &sp) ? sp.splits : tile_splits(M, N, Kp);
   }
   if (gemm_f32_small(M, N)) return 1;
   const int bm = bm_for_f32(M);

@@ -90,7 +90,7 @@ constexpr int STREAM_MAX_M = 192;
 struct StreamPlan {
   int fm, cb, splits;  // 32-row blocks, 32-column blocks per tile, K splits over workgroups
 };
-bool stream_plan(int M, int N, int Kp, int epi, StreamPlan* p);
+bool stream_plan(int M, int N, int Kp, int epi, int max_splits, StreamPlan* p);
 hipError_t launch_gemm_stream(const StreamPlan& p, int epi, const GemmArgs& a, hipStream_t s);
 // bf16 GEMM on 288 x 256 tiles, and on 288 x 128 tiles with two k groups (not with fixed_order); with
 // splits > 1 partial sums only.  Neither takes EPI_STORE_F32.

@@ -285,8 +285,10 @@ static hipError_t stream_launch_cb(int cb, int epi, const GemmArgs& a, hipStream
 // (us): 4 per pass of 256 workgroups, the fragments a workgroup loads at 55 GB/s per CU, not less
 // than the weights at 6.2 TB/s, and for a split the fp32 sums written at 4 TB/s and the reduction
 // that follows (2 more than the norm it is fused with after the residual projections, else 5).
-// Equal costs go to the plan with more workgroups, then to the wider tile.
-bool stream_plan(int M, int N, int Kp, int epi, StreamPlan* p) {
+// Equal costs go to the plan with more workgroups, then to the wider tile.  max_splits (what the
+// tiles of af_gemm.hip would split) bounds the fp32 sums: a caller's fixed scratch then holds every
+// step that it held with those tiles.  No plan of the 7B shape is held back by it.
+bool stream_plan(int M, int N, int Kp, int epi, int max_splits, StreamPlan* p) {
   if (M > STREAM_MAX_M) return false;
   const int fm = (M + 31) / 32, nb = (N + 31) / 32, units = Kp / 64;
   double best = 0;
@@ -294,6 +296,7 @@ bool stream_plan(int M, int N, int Kp, int epi, StreamPlan* p) {
   p->fm = 0;
   for (int cb = 1; cb <= stream_max_cb(fm); ++cb)
     for (int S : {1, 2, 3, 4, 6, 8}) {
+      if (S > max_splits) break;
       if (S > 4 && cb > 1) continue;  // short K ranges: a tile's prologue and sum weigh too much
       if (units / S < (S > 1 ? 8 : fm > 5 ? stream_ring(fm, cb) : 1)) continue;
       const int wg = (nb + cb - 1) / cb * S, passes = (wg + 255) / 256;

@@ -127,3 +127,17 @@ def test_noalloc_rejects_a_step_beyond_its_scratch():
     assert bool(torch.all(hid == 3.0))  # nothing ran
     ring.close()
     w.close()
+
+
+def test_noalloc_holds_a_wide_model_at_few_rows():
+    """147 rows of a model wider than the 7B shape: the split sums of the few-row projections stay
+    within what the 128-column tiles need, or the step would no longer fit the scratch array."""
+    shape = wl.ModelShape(n_layers=1, d_model=7424, n_heads=58, head_dim=128, d_ff=19952, vocab=512)
+    g, layers = wl.model_weights(shape, seed=1, device="cuda")
+    w = af.Weights(shape, g, layers)
+    del g, layers
+    rings = _rings(shape, 4, 192, "noalloc wide")
+    for r in rings:
+        for rid in (1, 2):
+            r.append(rid, 20 + rid)
+    _run_pair(w, shape, rings, [(3, 0, 145), (1, 21, 1), (2, 22, 1)], "wide")
