@@ -63,6 +63,25 @@ def test_f32_small_tiles(M, N, K):
     _check(M, N, K, torch.float32)
 
 
+@pytest.mark.parametrize("M", [1, 34])
+@pytest.mark.parametrize("K", [256, 512, 1024, 2048])
+def test_f32_small_tiles_infinite_weight(M, K):
+    """An infinite weight in the last k of a column, past every whole batch of steps (K = 512, 1024
+    and 2048 leave four, two and four over): the column is infinite with the sign of its
+    activation and no other column is touched."""
+    N, col = 48, 20
+    x = wl.draw(("t_inf_x", M, K), (M, K), dtype=torch.float32, device="cuda")
+    w = wl.draw(("t_inf_w", N, K), (N, K), std=0.02, dtype=torch.float32, device="cuda")
+    y, clean = torch.empty((M, N), device="cuda"), torch.empty((M, N), device="cuda")
+    af.op_linear(x, w, clean)
+    w[col, K - 1] = float("inf")
+    af.op_linear(x, w, y)
+    torch.cuda.synchronize()
+    assert torch.equal(y[:, col], torch.sign(x[:, K - 1]) * float("inf"))
+    keep = [c for c in range(N) if c != col]
+    assert torch.equal(y[:, keep], clean[:, keep])
+
+
 def test_step_tables_of_calls_in_flight():
     """Calls whose tables differ, sent without waiting, twice round the staging buffers and with
     tables that outgrow them on the way: every call reads its own tables."""
