@@ -20,20 +20,18 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lg = lane >> 4;
   const int n_mt = (a.M + 15) / 16;
   const int mt = blockIdx.x % n_mt, nt = blockIdx.x / n_mt;
-  const int n_blocks = a.N >> 4, ksteps = a.Kp >> 5;  // a wave takes steps wave, wave + 4, ...
+  const int n_blocks = a.N >> 4, ksteps = a.Kp >> 5;
   // rows past M repeat the last one and are never stored; k past K meets zero weights
   const float* arow = (const float*)a.A + (size_t)min(mt * 16 + lr, a.M - 1) * a.lda;
   const float* brow[2];
 #pragma unroll
   for (int n = 0; n < 2; ++n) brow[n] = (const float*)a.B + (size_t)min(2 * nt + n, n_blocks - 1) * a.bstride + lane * 8;
   f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-  // NU of this wave's steps from step i on: every load first, then the products
-  auto steps = [&](auto nu_c, int i) {
-    constexpr int NU = decltype(nu_c)::value;
-    frag x[NU], w[NU][2];
+  for (int k0 = wave; k0 < ksteps; k0 += 4 * UN) {
+    frag x[UN], w[UN][2];
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int ks = 4 * (i + u) + wave, k = ks * 32 + lg * 8;
+    for (int u = 0; u < UN; ++u) {
+      const int ks = min(k0 + 4 * u, ksteps - 1), k = ks * 32 + lg * 8;
       ((f32x4*)&x[u])[0] = *(const f32x4*)(arow + min(k, a.K - 4));
       ((f32x4*)&x[u])[1] = *(const f32x4*)(arow + min(k + 4, a.K - 4));
 #pragma unroll
@@ -41,26 +39,14 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmArgs a) {
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
+    for (int u = 0; u < UN; ++u) {
+      // a step past the last one has loaded that one again: it adds nothing (not a product with
+      // zeros, which an infinite weight would make NaN); the same for every lane of the wave
+      if (UN > 2 && __builtin_amdgcn_readfirstlane(k0 + 4 * u) >= ksteps) break;
       // weights first: lane l then holds columns 4 lg .. 4 lg + 3 of row lr
 #pragma unroll
       for (int n = 0; n < 2; ++n) acc[n] = Mma<float>::mma(w[u][n], x[u], acc[n]);
     }
-  };
-  // Kp is a multiple of 256: every wave has the same, even number of steps.  What UN leaves over is
-  // done as two or four steps, never as a step repeated with zeros in it: zero times an infinite
-  // weight is no zero.
-  const int n_steps = ksteps >> 2;
-  int i = 0;
-  for (; i + UN <= n_steps; i += UN) steps(std::integral_constant<int, UN>{}, i);
-  if constexpr (UN > 4) {
-    if (n_steps - i >= 4) {
-      steps(std::integral_constant<int, 4>{}, i);
-      i += 4;
-    }
-  }
-  if constexpr (UN > 2) {
-    if (n_steps - i >= 2) steps(std::integral_constant<int, 2>{}, i);
   }
 #pragma unroll
   for (int n = 0; n < 2; ++n) *(f32x4*)T_[wave][n][lane] = acc[n];

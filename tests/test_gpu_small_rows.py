@@ -66,9 +66,9 @@ def test_f32_small_tiles(M, N, K):
 @pytest.mark.parametrize("M", [1, 34])
 @pytest.mark.parametrize("K", [256, 512, 1024, 2048])
 def test_f32_small_tiles_infinite_weight(M, K):
-    """An infinite weight in the last k of a column, past every whole batch of steps (K = 512, 1024
-    and 2048 leave four, two and four over): the column is infinite with the sign of its
-    activation and no other column is touched."""
+    """An infinite weight in the last k of a column, where a wave's last batch of six steps is not
+    full (K = 512, 1024 and 2048: four, two and four steps): the column is infinite with the sign
+    of its activation and no other column is touched."""
     N, col = 48, 20
     x = wl.draw(("t_inf_x", M, K), (M, K), dtype=torch.float32, device="cuda")
     w = wl.draw(("t_inf_w", N, K), (N, K), std=0.02, dtype=torch.float32, device="cuda")
