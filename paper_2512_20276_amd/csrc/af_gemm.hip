@@ -838,17 +838,18 @@ static hipError_t gemm_launch_9(int epi, const GemmArgs& a, hipStream_t s) {
   return gemm32_launch<9, true>(epi, a, s);
 }
 
-// Split-K factor of the bf16 tiles of this file.
-static int tile_splits(int M, int N, int Kp) {
-  if (const int S = c6_narrow(M, N, Kp)) return S;
-  if (const int S = c6_wide_splits(M, N, Kp)) return S;
+// The plan of the bf16 tiles of this file.
+TilePlan tile_plan(int M, int N, int Kp) {
+  const int mb = (M + 31) / 32, nb = (N + 31) / 32;
+  auto plan = [&](int fm, int cols, int S) { return TilePlan{fm, S, (mb + fm - 1) / fm * ((nb + cols - 1) / cols) * S}; };
+  if (const int S = c6_narrow(M, N, Kp)) return plan(c6_fm(M), 4, S);
+  if (const int S = c6_wide_splits(M, N, Kp)) return plan(c6_fm(M), C6_NW, S);
   const int fm = fm_for(M);
-  const int tiles = (((M + 31) / 32 + fm - 1) / fm) * (((N + 31) / 32 + 3) / 4);
-  return splits_for(tiles, Kp / gemm_k_align());
+  return plan(fm, 4, splits_for(plan(fm, 4, 1).wg, Kp / gemm_k_align()));
 }
 // The streaming plan of a launch, if it takes that kernel.
 static bool stream_plan_for(int M, int N, int Kp, int epi, StreamPlan* p) {
-  return M <= STREAM_MAX_M && stream_plan(M, N, Kp, epi, tile_splits(M, N, Kp), p);
+  return M <= STREAM_MAX_M && stream_plan(M, N, Kp, epi, tile_plan(M, N, Kp), p);
 }
 
 static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) {
@@ -893,7 +894,7 @@ static hipError_t gemm_dispatch_bf16(int epi, const GemmArgs& a, hipStream_t s) 
 int gemm_splits(int dtype, int epi, int M, int N, int Kp) {
   if (dtype == AF_BF16) {
     StreamPlan sp;
-    return stream_plan_for(M, N, Kp, epi, &sp) ? sp.splits : tile_splits(M, N, Kp);
+    return stream_plan_for(M, N, Kp, epi, &sp) ? sp.splits : tile_plan(M, N, Kp).splits;
   }
   if (gemm_f32_small(M, N)) return 1;
   const int bm = bm_for_f32(M);

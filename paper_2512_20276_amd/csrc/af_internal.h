@@ -85,12 +85,19 @@ struct AttnArgs {
 
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs& a, hipStream_t s);
 hipError_t launch_attention(int dtype, int head_dim, const AttnArgs& a, int n_tiles, hipStream_t s);
+// The plan of the bf16 tiles of af_gemm.hip for a projection: 32-row blocks of a tile, K splits over
+// workgroups, workgroups.
+struct TilePlan {
+  int fm, splits, wg;
+};
+TilePlan tile_plan(int M, int N, int Kp);
 // bf16 GEMM with the K range split over a workgroup's waves, for up to STREAM_MAX_M rows.
 constexpr int STREAM_MAX_M = 192;
 struct StreamPlan {
   int fm, cb, splits;  // 32-row blocks, 32-column blocks per tile, K splits over workgroups
 };
-bool stream_plan(int M, int N, int Kp, int epi, int max_splits, StreamPlan* p);
+// False where the tiles do it (p is then undefined).
+bool stream_plan(int M, int N, int Kp, int epi, const TilePlan& tiles, StreamPlan* p);
 hipError_t launch_gemm_stream(const StreamPlan& p, int epi, const GemmArgs& a, hipStream_t s);
 // bf16 GEMM on 288 x 256 tiles, and on 288 x 128 tiles with two k groups (not with fixed_order); with
 // splits > 1 partial sums only.  Neither takes EPI_STORE_F32.

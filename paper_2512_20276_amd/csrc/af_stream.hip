@@ -281,14 +281,54 @@ static hipError_t stream_launch_cb(int cb, int epi, const GemmArgs& a, hipStream
   }
 }
 
-// Tile width and K splits for up to STREAM_MAX_M rows, from what a launch was measured to cost
-// (us): 4 per pass of 256 workgroups, the fragments a workgroup loads at 55 GB/s per CU, not less
-// than the weights at 6.2 TB/s, and for a split the fp32 sums written at 4 TB/s and the reduction
-// that follows (2 more than the norm it is fused with after the residual projections, else 5).
-// Equal costs go to the plan with more workgroups, then to the wider tile.  max_splits (what the
-// tiles of af_gemm.hip would split) bounds the fp32 sums: a caller's fixed scratch then holds every
-// step that it held with those tiles.  No plan of the 7B shape is held back by it.
-bool stream_plan(int M, int N, int Kp, int epi, int max_splits, StreamPlan* p) {
+// Whether the streaming plan p (wg workgroups) is taken, against the tiles that split K over
+// workgroups only.  Both were timed over every plan of ten model shapes (d 512 to 8192) and of LM
+// heads of 4096 to 128256 columns, these with cached weights and with weights that others had
+// displaced; where the lines lie, us tiles -> streamed:
+//  - It pays where the tiles' workgroups are few or their splits many: 64 rows, gate/up of the 7B
+//    shape 48.0 -> 38.1; 192 rows, N 5632, K 1024 24.9 -> 11.8.
+//  - An LM head of which the tiles fill the GPU unsplit: 96 rows, N 32000, 13.2 -> 15.9 at K 512 and
+//    26.9 -> 29.8 at K 2048 (cached), 90.5 -> 93.4 at K 4096 (displaced).  Storing a tile's fp32
+//    logits and adding the waves' sums cost the same at any K, so only long K pays (K 8192
+//    142.9 -> 141.1; on 96-column tiles N 22016, K 5120 83.2 -> 80.1), and with one row block none.
+//    Split heads on 128-column tiles: 128 rows, N 8192, K 4096 35.7 -> 39.5.
+//  - 128-column streamed tiles share less than the tiles of that width do.  Split more than two ways
+//    they pay over long K only (96 rows, N 8192: K 28672 97.8 -> 91.7, K 8192 42.0 -> 46.9), and with
+//    fewer workgroups than the tiles not at all (160 rows, N 5120, K 13824 51.0 -> 53.6).
+//  - Six row blocks: a tile of at most 96 columns.  Two passes of it for one of the tiles': N 27648,
+//    K 5120 84.6 -> 103.6, LM head N 32000, K 4096 71.6 -> 89.4.  Wide or split tiles are no faster
+//    than the 160-row tiles (7B shape: QKV 42.2 -> 42.8, O 25.6 -> 25.9, N 3072, K 3072 21.6 -> 23.0);
+//    narrow ones are (N 11008, K 2048 30.4 -> 26.2), wide ones over long K (N 24576, K 8192
+//    123.5 -> 117.4), and split ones against the 224-row tiles over short K (N 6144, K 2048
+//    29.3 -> 26.6; K 8192 56.5 -> 58.9).
+static bool stream_pays(const StreamPlan& p, int wg, int Kp, int epi, const TilePlan& tiles) {
+  if (epi == EPI_STORE_F32) {
+    if (tiles.splits == 1) return p.fm > 1 && p.fm < 6 && Kp >= (p.cb == 4 ? 8192 : 5120);
+    if (p.cb == 4) return false;
+  }
+  if (p.fm == 6) {
+    if (wg > 256) return false;
+    if (p.splits == 1) return p.cb == 1 || (p.cb == 2 ? Kp <= 6144 : Kp >= 8192);
+    return p.cb == 1 || (tiles.fm == 7 && Kp <= 3072);
+  }
+  // one row block, 128 columns, unsplit: the tile's waves share the activations and it is 1 % faster
+  // (61.5 against 62.1 us for the LM head of 7 rows with its norm and argmax)
+  if (p.fm == 1 && p.cb == 4 && p.splits == 1) return false;
+  if (p.cb >= 3 && p.splits > 2 && wg < tiles.wg) return false;
+  return !(p.cb == 4 && p.splits > 2 && Kp / p.splits < 4096);
+}
+
+// Tile width and K splits for up to STREAM_MAX_M rows: the plan of the least estimate (us) of 4 per
+// pass of 256 workgroups, the fragments a workgroup loads at 55 GB/s per CU, not less than the
+// weights at 6.2 TB/s, and for a split the fp32 sums written at 4 TB/s and the reduction that
+// follows (2 more than the norm it is fused with after the residual projections, else 5).  The
+// estimate only ranks streaming plans: 55 GB/s is what weights and activations reach at best, with
+// both in flight a CU loads 37 to 46, so gate/up of the 7B shape at 135 rows is put at 42 us and
+// takes 55.  Against the best of all plans the ranking loses 1 to 2 % over the ten shapes.
+// Equal costs go to the plan with more workgroups, then to the wider tile.  The tiles' splits bound
+// the fp32 sums: a caller's fixed scratch then holds every step that it held with those tiles.  No
+// plan of the 7B shape is held back by it.
+bool stream_plan(int M, int N, int Kp, int epi, const TilePlan& tiles, StreamPlan* p) {
   if (M > STREAM_MAX_M) return false;
   const int fm = (M + 31) / 32, nb = (N + 31) / 32, units = Kp / 64;
   double best = 0;
@@ -296,7 +336,7 @@ bool stream_plan(int M, int N, int Kp, int epi, int max_splits, StreamPlan* p) {
   p->fm = 0;
   for (int cb = 1; cb <= stream_max_cb(fm); ++cb)
     for (int S : {1, 2, 3, 4, 6, 8}) {
-      if (S > max_splits) break;
+      if (S > tiles.splits) break;
       if (S > 4 && cb > 1) continue;  // short K ranges: a tile's prologue and sum weigh too much
       if (units / S < (S > 1 ? 8 : fm > 5 ? stream_ring(fm, cb) : 1)) continue;
       const int wg = (nb + cb - 1) / cb * S, passes = (wg + 255) / 256;
@@ -308,10 +348,7 @@ bool stream_plan(int M, int N, int Kp, int epi, int max_splits, StreamPlan* p) {
         best_wg = wg;
       }
     }
-  // one pass of 128-column tiles over a single row block, unsplit (the LM head of a few rows):
-  // gemm32_kernel, which shares the activations between its waves, is 1 % faster (61.5 against
-  // 62.1 us with the norm and the argmax)
-  return p->fm > 0 && !(p->fm == 1 && p->cb == 4 && p->splits == 1);
+  return p->fm > 0 && stream_pays(*p, best_wg, Kp, epi, tiles);
 }
 
 hipError_t launch_gemm_stream(const StreamPlan& p, int epi, const GemmArgs& a, hipStream_t s) {

@@ -1,0 +1,91 @@
+"""Which kernel a projection takes, on the CPU: the library's planner (host code) is called by its
+C++ name.  The lists hold shapes on which both kernels were timed; the times are us."""
+import ctypes as C
+import random
+
+import pytest
+
+import paper_2512_20276_amd as af
+
+EPI_STORE_F32, EPI_RESID, EPI_SWIGLU, EPI_QKV = 1, 2, 3, 4
+
+
+class TilePlan(C.Structure):
+    _fields_ = [("fm", C.c_int), ("splits", C.c_int), ("wg", C.c_int)]
+
+
+class StreamPlan(C.Structure):
+    _fields_ = [("fm", C.c_int), ("cb", C.c_int), ("splits", C.c_int)]
+
+
+_tile = af.lib["_ZN2af9tile_planEiii"]
+_tile.restype, _tile.argtypes = TilePlan, [C.c_int] * 3
+_stream = af.lib["_ZN2af11stream_planEiiiiRKNS_8TilePlanEPNS_10StreamPlanE"]
+_stream.restype, _stream.argtypes = C.c_bool, [C.c_int] * 4 + [C.POINTER(TilePlan), C.POINTER(StreamPlan)]
+
+
+def padk(k):
+    return (k + 255) // 256 * 256
+
+
+def stream_plan(epi, M, N, K):
+    """(row blocks, column blocks, K splits) of the streaming kernel, or None where the tiles run."""
+    p = StreamPlan()
+    t = _tile(M, N, padk(K))
+    return (p.fm, p.cb, p.splits) if _stream(M, N, padk(K), epi, C.byref(t), C.byref(p)) else None
+
+
+@pytest.mark.parametrize("epi,M,N,K", [
+    (EPI_STORE_F32, 161, 32000, 4096),   # tiles 65.4, streamed 85.1: two passes for one
+    (EPI_STORE_F32, 192, 32000, 4096),   # 71.6, 89.4
+    (EPI_STORE_F32, 192, 128256, 2048),  # tiles four passes, streamed six
+    (EPI_STORE_F32, 64, 32000, 512),     # 13.3, 13.9
+    (EPI_STORE_F32, 96, 32000, 1024),    # 18.9, 21.5
+    (EPI_STORE_F32, 160, 32000, 2048),   # 31.9, 34.6
+    (EPI_STORE_F32, 128, 32000, 4096),   # weights displaced from the caches: 92.5, 95.0
+    (EPI_STORE_F32, 16, 24576, 1024),    # 12.6, 13.4
+    (EPI_STORE_F32, 128, 8192, 4096),    # 35.7, 39.5
+    (EPI_SWIGLU, 161, 27648, 5120),      # 84.1, 103.3
+    (EPI_SWIGLU, 192, 57344, 8192),      # 253.9, 288.3
+    (EPI_RESID, 192, 8192, 28672),       # 126.9, 145.0
+    (EPI_RESID, 192, 3072, 3072),        # 21.6, 23.0
+    (EPI_RESID, 96, 8192, 8192),         # 42.0, 46.9
+    (EPI_RESID, 160, 5120, 13824),       # 51.0, 53.6
+])
+def test_tiles_where_streaming_is_slower(epi, M, N, K):
+    assert stream_plan(epi, M, N, K) is None
+
+
+@pytest.mark.parametrize("epi,M,N,K,plan", [
+    (EPI_SWIGLU, 16, 22016, 4096, (1, 3, 1)),    # tiles 36.0, streamed 34.0
+    (EPI_SWIGLU, 64, 22016, 4096, (2, 3, 1)),    # 48.0, 38.1
+    (EPI_SWIGLU, 135, 22016, 4096, (5, 3, 1)),   # 60.3, 55.2
+    (EPI_QKV, 160, 12288, 4096, (5, 3, 2)),      # 43.8, 41.8
+    (EPI_RESID, 160, 4096, 4096, (5, 2, 4)),     # 26.8, 25.1
+    (EPI_RESID, 96, 8192, 28672, (3, 4, 4)),     # 97.8, 91.7
+    (EPI_SWIGLU, 192, 5632, 1024, (6, 1, 1)),    # 24.9, 11.8
+    (EPI_SWIGLU, 192, 11008, 2048, (6, 2, 1)),   # 30.4, 26.2
+    (EPI_QKV, 192, 6144, 2048, (6, 3, 4)),       # 29.3, 26.6
+    (EPI_QKV, 192, 24576, 8192, (6, 3, 1)),      # 123.5, 117.4
+    (EPI_STORE_F32, 33, 4096, 1024, (2, 1, 1)),  # 11.2, 7.5
+    (EPI_STORE_F32, 96, 22016, 5120, (3, 3, 1)),  # 83.2, 80.1
+])
+def test_streamed_where_it_is_faster(epi, M, N, K, plan):
+    assert stream_plan(epi, M, N, K) == plan
+
+
+def test_streamed_sums_fit_where_the_tiles_sums_fit():
+    """A plan splits K no further than the tiles would, and every split has the k steps that the
+    kernel asks for."""
+    rng = random.Random(7)
+    for _ in range(4000):
+        epi, M = rng.choice([EPI_STORE_F32, EPI_RESID, EPI_SWIGLU, EPI_QKV]), rng.randint(1, 192)
+        N, K = 16 * rng.randint(1, 3000), 32 * rng.randint(1, 400)
+        p = stream_plan(epi, M, N, K)
+        if p is None:
+            continue
+        fm, cb, S = p
+        assert fm == (M + 31) // 32 and 1 <= cb <= (4 if fm < 6 else 3)
+        assert S <= _tile(M, N, padk(K)).splits
+        assert padk(K) // 64 // S >= (40 // (fm + cb) if fm > 5 else 1)
+    assert stream_plan(EPI_RESID, 193, 4096, 4096) is None
