@@ -241,8 +241,36 @@ static int bm_for_f32(int M) {
   return ((M + 95) / 96) * 96 < ((M + 127) / 128) * 128 ? 96 : 128;
 }
 
+// Split-K factor of these tiles.
+static int f32_tile_splits(int M, int N, int Kp) {
+  const int bm = bm_for_f32(M), tiles = (M + bm - 1) / bm * ((N + 127) / 128);
+  return tiles >= 160 ? 1 : std::max(1, std::min(std::min(4, 256 / tiles), Kp / gemm_k_align()));
+}
+
+// The 16 x 32 tiles (gemm_f32_small_kernel) where they take less time than these: they are many and
+// short where these leave the GPU idle, but load an activation row once per 32 columns instead of
+// 128 and a weight once per 16 rows instead of 32, 96 or 128.  Both times (us) are estimated from a
+// fixed part and what a pass of 256 workgroups costs per 1000 k; the constants are fitted to 2000
+// shapes of 1 to 1000 rows, N 256 to 32000, K 256 to 8192 (6 % rms; a shape where the estimates
+// differ by less than 3 % stays with these tiles).  Small tiles against these: 34 rows, N 768, K 256
+// 6.6 against 27.8 us; 32 rows, K 4096: N 4096 28.2 against 43.4, N 16384 81.5 against 54.3;
+// 128 rows, N 4096, K 1024 28.3 against 33.8; 80 rows, N 6144, K 4096 84.5 against 66.0.  At most
+// 1024 small tiles, four a CU: all that was timed.
+bool gemm_f32_small(int M, int N, int Kp) {
+  const int wg = (M + 15) / 16 * ((N + 31) / 32);
+  if (wg > 1024) return false;
+  const double k = Kp / 1000.0;
+  double small = 5.15 + (3.15 * ((wg + 255) / 256) + 1.85 * wg / 256) * k;
+  if (M > 128) small *= 0.95;  // nine row tiles and more share a weight (512 rows, N 1024, K 2816: 51.9 against 65.9)
+  const int bm = bm_for_f32(M), S = f32_tile_splits(M, N, Kp);
+  const int passes = ((M + bm - 1) / bm * ((N + 127) / 128) * S + 255) / 256;
+  const double fixed = bm == 32 ? 5.4 : bm == 96 ? 7.6 : 8.8, per_k = bm == 32 ? 21 : bm == 96 ? 52 : 65;
+  const double sums = S == 1 ? 0 : bm == 32 ? 3.0 : bm == 96 ? 4.6 : 5.3;
+  return small < fixed + per_k * passes * k / S + sums;
+}
+
 static hipError_t gemm_dispatch_f32(int epi, const GemmArgs& a, hipStream_t s) {
-  if (!a.fixed_order && a.splits == 1 && gemm_f32_small(a.M, a.N)) return launch_gemm_f32_small(epi, a, s);
+  if (!a.fixed_order && a.splits == 1 && gemm_f32_small(a.M, a.N, a.Kp)) return launch_gemm_f32_small(epi, a, s);
   const int bm = bm_for_f32(a.M);
   hipError_t e = bm == 32 ? gemm_launch_cfg<float, CfgF32S>(epi, a, s)
                  : bm == 96 ? gemm_launch_cfg<float, CfgF32M>(epi, a, s) : gemm_launch_cfg<float, CfgF32L>(epi, a, s);
@@ -896,11 +924,7 @@ int gemm_splits(int dtype, int epi, int M, int N, int Kp) {
     StreamPlan sp;
     return stream_plan_for(M, N, Kp, epi, &sp) ? sp.splits : tile_plan(M, N, Kp).splits;
   }
-  if (gemm_f32_small(M, N)) return 1;
-  const int bm = bm_for_f32(M);
-  const int tiles = ((M + bm - 1) / bm) * ((N + 127) / 128);
-  if (tiles >= 160) return 1;
-  return std::max(1, std::min(std::min(4, 256 / tiles), Kp / gemm_k_align()));
+  return gemm_f32_small(M, N, Kp) ? 1 : f32_tile_splits(M, N, Kp);
 }
 
 int gemm_k_align() { return 256; }

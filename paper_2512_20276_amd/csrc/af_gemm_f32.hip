@@ -91,8 +91,4 @@ hipError_t launch_gemm_f32_small(int epi, const GemmArgs& a, hipStream_t s) {
   return a.Kp == 256 ? f32_small_launch<2>(epi, a, s) : f32_small_launch<6>(epi, a, s);
 }
 
-// Taken while its workgroups number at most four per CU: past that the grid fills the GPU with
-// the larger tiles as well, which load each activation row once per 128 columns instead of 32.
-bool gemm_f32_small(int M, int N) { return (long)((M + 15) / 16) * ((N + 31) / 32) <= 1024; }
-
 }  // namespace af

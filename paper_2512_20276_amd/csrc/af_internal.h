@@ -104,7 +104,7 @@ hipError_t launch_gemm_stream(const StreamPlan& p, int epi, const GemmArgs& a, h
 hipError_t launch_gemm_wide(int epi, const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_ksplit(int epi, const GemmArgs& a, hipStream_t s);
 // fp32 GEMM on 16 x 32 tiles, where gemm_f32_small says so (unsplit).
-bool gemm_f32_small(int M, int N);
+bool gemm_f32_small(int M, int N, int Kp);
 hipError_t launch_gemm_f32_small(int epi, const GemmArgs& a, hipStream_t s);
 // The step tables on their way to the device: n16 chunks of 16 bytes from pinned host memory, read
 // by extra workgroups of the call's first kernel (a copy command of its own takes 4 us, longer

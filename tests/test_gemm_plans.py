@@ -20,6 +20,8 @@ class StreamPlan(C.Structure):
 
 _tile = af.lib["_ZN2af9tile_planEiii"]
 _tile.restype, _tile.argtypes = TilePlan, [C.c_int] * 3
+_f32_small = af.lib["_ZN2af14gemm_f32_smallEiii"]
+_f32_small.restype, _f32_small.argtypes = C.c_bool, [C.c_int] * 3
 _stream = af.lib["_ZN2af11stream_planEiiiiRKNS_8TilePlanEPNS_10StreamPlanE"]
 _stream.restype, _stream.argtypes = C.c_bool, [C.c_int] * 4 + [C.POINTER(TilePlan), C.POINTER(StreamPlan)]
 
@@ -89,3 +91,27 @@ def test_streamed_sums_fit_where_the_tiles_sums_fit():
         assert S <= _tile(M, N, padk(K)).splits
         assert padk(K) // 64 // S >= (40 // (fm + cb) if fm > 5 else 1)
     assert stream_plan(EPI_RESID, 193, 4096, 4096) is None
+
+
+@pytest.mark.parametrize("M,N,K,small", [
+    (34, 768, 256, True),       # tiles of 96 x 128 27.8, of 16 x 32 6.6
+    (34, 256, 688, True),       # 23.7, 7.6
+    (200, 1376, 256, True),     # 26.0, 7.8
+    (3, 512, 256, True),        # 11.2, 7.0
+    (16, 12288, 4096, True),    # 56.9, 51.5
+    (32, 4096, 4096, True),     # 43.4, 28.2
+    (128, 4096, 1024, True),    # 33.8, 28.3
+    (512, 1024, 2048, True),    # 49.2, 40.0
+    (512, 1024, 2816, True),    # 65.9, 51.9
+    (17, 12288, 4096, False),   # 49.0, 64.9
+    (32, 16384, 4096, False),   # 54.3, 82.0
+    (32, 16384, 512, False),    # 16.2, 19.3
+    (24, 6144, 1024, False),    # 15.0, 18.5
+    (16, 9984, 4096, False),    # 37.3, 42.8
+    (80, 6144, 4096, False),    # 66.0, 84.5
+    (144, 3072, 8192, False),   # 121.6, 160.6
+    (400, 1024, 8192, False),   # 120.8, 146.9
+    (64, 8192, 8192, False),    # 118.2, 149.9
+])
+def test_small_fp32_tiles_where_they_are_faster(M, N, K, small):
+    assert _f32_small(M, N, padk(K)) is small

@@ -63,6 +63,12 @@ def test_f32_small_tiles(M, N, K):
     _check(M, N, K, torch.float32)
 
 
+@pytest.mark.parametrize("M,N,K", [(32, 16384, 512), (24, 6144, 1024), (80, 6144, 2048), (144, 3072, 2048)])
+def test_f32_wide_tiles_of_few_rows(M, N, K):
+    """Few rows that the 32- and 96-row fp32 tiles do faster than the 16 x 32 ones, K split and not."""
+    _check(M, N, K, torch.float32)
+
+
 @pytest.mark.parametrize("M", [1, 34])
 @pytest.mark.parametrize("K", [256, 512, 1024, 2048])
 def test_f32_small_tiles_infinite_weight(M, K):
