@@ -29,11 +29,14 @@ struct Layer {
 // K of the fragment-tiled weights: padded so the GEMM's k loop has no partial unrolled block.
 inline int padk(int k) { return (k + gemm_k_align() - 1) / gemm_k_align() * gemm_k_align(); }
 
-// Pinned staging of step tables: STAGE_GROUPS groups of STAGE_PER_GROUP buffers, used in turn.  An
-// event behind a group's last reader guards the whole group (the calls of one weights object are
-// ordered).  One event a group, since an event between two kernels keeps the second waiting: 5.7 us
-// of the stream when every call recorded one.
-constexpr int STAGE_GROUPS = 4, STAGE_PER_GROUP = 8;
+// Pinned staging of step tables: STAGE_GROUPS groups of buffers, used in turn.  An event behind a
+// group's last reader guards the whole group (the calls of one weights object are ordered).  One
+// event a group, since an event between two kernels keeps the second waiting: 5.7 us of the stream
+// when every call recorded one.  The longer the tables, the fewer buffers a group has: eight of 16 KB
+// (tables of some 1900 rows), one from 128 KB on, so that the buffers take 512 KB, or four tables
+// where those are more.
+constexpr int STAGE_GROUPS = 4;
+constexpr size_t STAGE_GROUP_WORDS = 32 * 1024;
 struct StageGroup {
   hipEvent_t done = nullptr;
   bool pending = false;
@@ -74,8 +77,9 @@ struct af_weights {
 
   int32_t* desc_dev = nullptr;
   size_t desc_cap = 0;
-  int32_t* stage_host = nullptr;  // one buffer of desc_cap words per staged call
+  int32_t* stage_host = nullptr;  // the buffers, of desc_cap words each
   StageGroup stage[STAGE_GROUPS];
+  int stage_per_group = 1;
   int stage_next = 0;             // the buffer of the next call
 
   uint32_t options = 0;
@@ -277,20 +281,20 @@ void build_desc(const af_segment* segs, int n_seg, int M, StepDesc& sd) {
 af_status stage_desc(af_weights* w, const StepDesc& sd, int32_t** out) {
   const size_t n = (sd.buf.size() + 3) / 4 * 4;  // whole 16-byte chunks
   if (n > w->desc_cap) {
-    if (w->desc_dev) {
-      AF_HIP(hipDeviceSynchronize());
-      for (StageGroup& g : w->stage) g.pending = false;
-      if (w->stage_host) (void)hipHostFree(w->stage_host);
-      w->stage_host = nullptr;
-      w->desc_cap = 0;
-      dev_free(w, w->desc_dev);
-      w->desc_dev = nullptr;
-    }
+    if (w->desc_dev) AF_HIP(hipDeviceSynchronize());
+    for (StageGroup& g : w->stage) g.pending = false;
+    if (w->stage_host) (void)hipHostFree(w->stage_host);
+    w->stage_host = nullptr;
+    w->stage_next = 0;
+    w->desc_cap = 0;
+    dev_free(w, w->desc_dev);
+    w->desc_dev = nullptr;
     size_t cap = 4096;
     while (cap < n) cap *= 2;
     AF_TRY(dev_alloc(w, (void**)&w->desc_dev, cap * 4));
+    w->stage_per_group = (int)std::max<size_t>(1, STAGE_GROUP_WORDS / cap);
     // coherent: a buffer's later contents are read by later kernels with no event in between
-    const size_t bytes = cap * 4 * STAGE_GROUPS * STAGE_PER_GROUP;
+    const size_t bytes = cap * 4 * STAGE_GROUPS * w->stage_per_group;
     hipError_t e = hipHostMalloc((void**)&w->stage_host, bytes, hipHostMallocCoherent);
     if (e != hipSuccess) {
       w->stage_host = nullptr;
@@ -299,7 +303,7 @@ af_status stage_desc(af_weights* w, const StepDesc& sd, int32_t** out) {
     }
     w->desc_cap = cap;
   }
-  StageGroup& g = w->stage[w->stage_next / STAGE_PER_GROUP];
+  StageGroup& g = w->stage[w->stage_next / w->stage_per_group];
   if (g.pending) {
     AF_HIP(hipEventSynchronize(g.done));
     g.pending = false;
@@ -314,9 +318,9 @@ af_status stage_desc(af_weights* w, const StepDesc& sd, int32_t** out) {
 // buffer.
 af_status staged_done(af_weights* w, hipStream_t s) {
   const int i = w->stage_next;
-  w->stage_next = (i + 1) % (STAGE_GROUPS * STAGE_PER_GROUP);
-  if ((i + 1) % STAGE_PER_GROUP) return AF_OK;
-  StageGroup& g = w->stage[i / STAGE_PER_GROUP];
+  w->stage_next = (i + 1) % (STAGE_GROUPS * w->stage_per_group);
+  if ((i + 1) % w->stage_per_group) return AF_OK;
+  StageGroup& g = w->stage[i / w->stage_per_group];
   AF_HIP(hipEventRecord(g.done, s));
   g.pending = true;
   return AF_OK;

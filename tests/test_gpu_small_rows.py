@@ -88,17 +88,40 @@ def test_f32_small_tiles_infinite_weight(M, K):
     assert torch.equal(y[:, keep], clean[:, keep])
 
 
+class _Busy:
+    """A bounded stretch of work (products of 8192 x 8192, about 1 ms each) that holds the stream back."""
+
+    def __init__(self):
+        self.a = torch.ones((8192, 8192), dtype=torch.bfloat16, device="cuda")
+        self.out = torch.empty_like(self.a)
+        self.end = torch.cuda.Event()
+
+    def start(self, n):
+        for _ in range(n):
+            torch.mm(self.a, self.a, out=self.out)
+        self.end.record()
+
+    def running(self):
+        return not self.end.query()
+
+
 def test_step_tables_of_calls_in_flight():
-    """Calls whose tables differ, sent without waiting, twice round the staging buffers and with
-    tables that outgrow them on the way: every call reads its own tables."""
+    """Calls whose tables differ, sent while the stream is held back: every staging buffer is in
+    flight when the host comes round to the first again, which then has to wait.  Twice round the 32
+    buffers, and after tables that outgrow them, of which there is room for 16 and for 4: every call
+    reads its own tables."""
     shape = wl.TINY
     g, layers = wl.model_weights(shape, seed=3, device="cuda")
-    n_req, rows = 12, 2500
-    order = [[(5 * i + j) % n_req for j in range(1 + i % n_req)] for i in range(72)]
+    n_req, rows, n_many = 12, 2500, 3300
+    base = wl.draw(("t_tab_x",), (100 + n_many * 10, shape.d_model), dtype=torch.float32, device="cuda")
+    # (requests of a call) ; "long" and "many" are the calls whose tables outgrow the buffers
+    order = [[(5 * i + j) % n_req for j in range(1 + i % n_req)] for i in range(40)]
 
     def all_calls(wait):
         w = af.Weights(shape, g, layers)
         ring = af.Ring(shape.n_layers, n_req + 1, 2560, shape.n_heads, shape.head_dim, dtype=torch.float32)
+        ring2 = af.Ring(shape.n_layers, n_many, 16, shape.n_heads, shape.head_dim, dtype=torch.float32)
+        busy = _Busy()
         segs = {}
         for r in range(n_req):
             slot = ring.append(r, 3 + r).slot
@@ -107,23 +130,45 @@ def test_step_tables_of_calls_in_flight():
             ring.write_kv(0, slot, 0, *kv)
             segs[r] = ring.append(r, 1)
         long = ring.append(n_req, rows)
-        out = []
-        for i, reqs in enumerate(order):
-            call = [segs[r] for r in reqs] if i != 40 else [long]
+        many = [ring2.append(r, 10) for r in range(n_many)]
+        for i, s in enumerate(many):
+            s.q_start, s.flags = 10 * i, af.AF_SEG_EMIT
+        many = af.segments_array(many)
+        long.q_start, long.flags = 0, af.AF_SEG_EMIT
+        long = af.segments_array([long])
+        # a request's row is the same in every call, so are the keys and values it writes
+        hidden = [base[torch.tensor(reqs, device="cuda")] for reqs in order]
+        arrays = []
+        for reqs in order:
+            call = [segs[r] for r in reqs]
             for row, s in enumerate(call):
                 s.q_start, s.flags = row, af.AF_SEG_EMIT
-            # a request's row is the same in every call, so are the keys and values it writes
-            ids = reqs if i != 40 else range(100, 100 + rows)
-            h = torch.stack([base[r] for r in ids])
-            af.packed_layer_forward(w, 0, h, af.segments_array(call), ring)
-            z = torch.empty((len(call), shape.vocab), dtype=torch.float32, device="cuda")
-            af.op_lm_head_argmax(w, h, af.segments_array(call), z)
+            arrays.append(af.segments_array(call))
+        out = []
+
+        def call(h, sa, r):
+            af.packed_layer_forward(w, 0, h, sa, r)
+            z = torch.empty((len(sa), shape.vocab), dtype=torch.float32, device="cuda")
+            af.op_lm_head_argmax(w, h, sa, z)
             if wait:
                 torch.cuda.synchronize()
-            out += [h, z]
+            out.extend([h, z])
+
+        for grow, buffers in ((None, 32), ((base[100:100 + rows], long, ring), 16), ((base[100:], many, ring2), 4)):
+            if grow is None:
+                call(hidden[0].clone(), arrays[0], ring)  # workspaces are allocated here
+            else:
+                call(grow[0].clone(), *grow[1:])
+            torch.cuda.synchronize()
+            if not wait:
+                busy.start(60)
+            # a call stages two tables (layer, head); the one above has taken the first two buffers
+            for i, (h, sa) in enumerate(zip(hidden, arrays)):
+                call(h.clone(), sa, ring)
+                if not wait and 2 * i + 4 == buffers:
+                    assert busy.running()  # the next call needs the first buffer again
         torch.cuda.synchronize()
         return out
 
-    base = wl.draw(("t_tab_x",), (100 + rows, shape.d_model), dtype=torch.float32, device="cuda")
     for i, (a, b) in enumerate(zip(all_calls(True), all_calls(False))):
         assert torch.equal(a, b), i
