@@ -301,9 +301,14 @@ static hipError_t stream_launch_cb(int cb, int epi, const GemmArgs& a, hipStream
 //    narrow ones are (N 11008, K 2048 30.4 -> 26.2), wide ones over long K (N 24576, K 8192
 //    123.5 -> 117.4), and split ones against the 224-row tiles over short K (N 6144, K 2048
 //    29.3 -> 26.6; K 8192 56.5 -> 58.9).
+//  - Short K: the waves' sums outweigh it.  Tiles that fill the GPU unsplit: 160 rows, N 27648, K 512
+//    16.6 -> 20.3, K 2048 36.1 -> 37.5; N 22016, K 512 15.4 -> 17.5 (64 rows 12.5 -> 11.6).  One row
+//    block at K 256, where a wave has four steps of a ring of up to twenty: N 768 6.3 -> 6.9.
 static bool stream_pays(const StreamPlan& p, int wg, int Kp, int epi, const TilePlan& tiles) {
+  const bool full = tiles.splits == 1 && tiles.wg >= 160;  // the tiles fill the GPU unsplit
+  if (p.fm == 1 && Kp <= 256) return false;
   if (epi == EPI_STORE_F32) {
-    if (tiles.splits == 1) return p.fm > 1 && p.fm < 6 && Kp >= (p.cb == 4 ? 8192 : 5120);
+    if (full) return p.fm > 1 && p.fm < 6 && Kp >= (p.cb == 4 ? 8192 : 5120);
     if (p.cb == 4) return false;
   }
   if (p.fm == 6) {
@@ -314,6 +319,7 @@ static bool stream_pays(const StreamPlan& p, int wg, int Kp, int epi, const Tile
   // one row block, 128 columns, unsplit: the tile's waves share the activations and it is 1 % faster
   // (61.5 against 62.1 us for the LM head of 7 rows with its norm and argmax)
   if (p.fm == 1 && p.cb == 4 && p.splits == 1) return false;
+  if (full && Kp < (p.cb == 4 ? 3072 : p.fm > 3 ? 1536 : 512)) return false;
   if (p.cb >= 3 && p.splits > 2 && wg < tiles.wg) return false;
   return !(p.cb == 4 && p.splits > 2 && Kp / p.splits < 4096);
 }

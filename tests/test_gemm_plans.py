@@ -53,6 +53,9 @@ def stream_plan(epi, M, N, K):
     (EPI_RESID, 192, 3072, 3072),        # 21.6, 23.0
     (EPI_RESID, 96, 8192, 8192),         # 42.0, 46.9
     (EPI_RESID, 160, 5120, 13824),       # 51.0, 53.6
+    (EPI_SWIGLU, 160, 27648, 512),       # 16.6, 20.3
+    (EPI_SWIGLU, 160, 22016, 512),       # 15.4, 17.5
+    (EPI_QKV, 1, 768, 256),              # 6.3, 6.9
 ])
 def test_tiles_where_streaming_is_slower(epi, M, N, K):
     assert stream_plan(epi, M, N, K) is None
