@@ -1,40 +1,10 @@
-"""Which kernel a projection takes, on the CPU: the library's planner (host code) is called by its
-C++ name.  The lists hold shapes on which both kernels were timed; the times are us."""
-import ctypes as C
+"""Which kernel a projection takes, on the CPU.  The lists hold shapes on which both kernels were
+timed; the times are us."""
 import random
 
 import pytest
 
-import paper_2512_20276_amd as af
-
-EPI_STORE_F32, EPI_RESID, EPI_SWIGLU, EPI_QKV = 1, 2, 3, 4
-
-
-class TilePlan(C.Structure):
-    _fields_ = [("fm", C.c_int), ("splits", C.c_int), ("wg", C.c_int)]
-
-
-class StreamPlan(C.Structure):
-    _fields_ = [("fm", C.c_int), ("cb", C.c_int), ("splits", C.c_int)]
-
-
-_tile = af.lib["_ZN2af9tile_planEiii"]
-_tile.restype, _tile.argtypes = TilePlan, [C.c_int] * 3
-_f32_small = af.lib["_ZN2af14gemm_f32_smallEiii"]
-_f32_small.restype, _f32_small.argtypes = C.c_bool, [C.c_int] * 3
-_stream = af.lib["_ZN2af11stream_planEiiiiRKNS_8TilePlanEPNS_10StreamPlanE"]
-_stream.restype, _stream.argtypes = C.c_bool, [C.c_int] * 4 + [C.POINTER(TilePlan), C.POINTER(StreamPlan)]
-
-
-def padk(k):
-    return (k + 255) // 256 * 256
-
-
-def stream_plan(epi, M, N, K):
-    """(row blocks, column blocks, K splits) of the streaming kernel, or None where the tiles run."""
-    p = StreamPlan()
-    t = _tile(M, N, padk(K))
-    return (p.fm, p.cb, p.splits) if _stream(M, N, padk(K), epi, C.byref(t), C.byref(p)) else None
+from tests.plans import (EPI_QKV, EPI_RESID, EPI_STORE_F32, EPI_SWIGLU, f32_small, padk, stream_plan, tile_plan)
 
 
 @pytest.mark.parametrize("epi,M,N,K", [
@@ -91,7 +61,7 @@ def test_streamed_sums_fit_where_the_tiles_sums_fit():
             continue
         fm, cb, S = p
         assert fm == (M + 31) // 32 and 1 <= cb <= (4 if fm < 6 else 3)
-        assert S <= _tile(M, N, padk(K)).splits
+        assert S <= tile_plan(M, N, K).splits
         assert padk(K) // 64 // S >= (40 // (fm + cb) if fm > 5 else 1)
     assert stream_plan(EPI_RESID, 193, 4096, 4096) is None
 
@@ -117,4 +87,4 @@ def test_streamed_sums_fit_where_the_tiles_sums_fit():
     (64, 8192, 8192, False),    # 118.2, 149.9
 ])
 def test_small_fp32_tiles_where_they_are_faster(M, N, K, small):
-    assert _f32_small(M, N, padk(K)) is small
+    assert f32_small(M, N, K) is small

@@ -1,15 +1,17 @@
 """GPU parity of the projection GEMMs at the edges of their tiles.
 
-bf16 up to 192 rows runs with K split over a workgroup's waves (one kernel instance per number of
-32-row blocks, tiles of 1 to 4 column blocks, 1 to 8 K splits); fp32 projections of up to 1024
-tiles of 16 x 32 run on those; bf16 tiles of 288 rows split k between two groups of waves.  Every element is held to what its arithmetic allows: fp32 sums of
-K products in any order lie within K 2^-24 sum |x w| of the exact value, and storing in bf16 adds
-at most 2^-8 of it.
+bf16 up to 192 rows runs with K split over a workgroup's waves where that is faster (one kernel
+instance per number of 32-row blocks and of column blocks; every one is run here, unsplit and with
+K split over workgroups, the planner saying which one a shape takes); fp32 projections run on 16 x
+32 tiles where those are faster; bf16 tiles of 288 rows split k between two groups of waves.  Every
+element is held to what its arithmetic allows: fp32 sums of K products in any order lie within
+K 2^-24 sum |x w| of the exact value, and storing in bf16 adds at most 2^-8 of it.
 """
 import pytest
 import torch
 
 import workload as wl
+from tests.plans import EPI_STORE, EPI_STORE_F32, f32_small, stream_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -31,10 +33,89 @@ def _check(M, N, K, dt):
     assert bool((err <= bound).all()), (M, N, K, float((err - bound).max()))
 
 
+def _bound(x, w, ref, dt):
+    """What the exact value and a result may differ by (float64 on the GPU)."""
+    b = (x.shape[1] + 8) * 2.0 ** -24 * (x.abs() @ w.abs().t())
+    return b + ref.abs() * 2.0 ** -8 if dt == torch.bfloat16 else b
+
+
+# (row blocks, column blocks, K splits) of an instance and a width and depth that take it
+STREAMED = [
+    (1, 1, 1, 48, 3072), (1, 1, 8, 48, 11008), (1, 2, 1, 9200, 512), (1, 2, 4, 3072, 5632), (1, 3, 1, 20464, 512),
+    (2, 1, 1, 48, 2048), (2, 1, 8, 48, 11008), (2, 2, 1, 9200, 256), (2, 2, 4, 3072, 3072), (2, 3, 1, 20464, 512),
+    (2, 3, 2, 9200, 4096), (2, 4, 1, 27632, 3072),
+    (3, 1, 1, 48, 1536), (3, 1, 8, 48, 11008), (3, 2, 1, 9200, 256), (3, 2, 4, 3072, 2816), (3, 3, 1, 20464, 512),
+    (3, 3, 4, 6128, 4096), (3, 4, 1, 27632, 3072), (3, 4, 2, 15344, 11008),
+    (4, 1, 1, 48, 1280), (4, 1, 8, 48, 11008), (4, 2, 1, 9200, 256), (4, 2, 4, 3072, 2048), (4, 3, 1, 20464, 1536),
+    (4, 3, 4, 6128, 2816), (4, 4, 1, 27632, 3072), (4, 4, 2, 15344, 5632),
+    (5, 1, 1, 48, 1280), (5, 1, 8, 48, 11008), (5, 2, 1, 9200, 256), (5, 2, 4, 3072, 2048), (5, 3, 1, 20464, 1536),
+    (5, 3, 4, 6128, 2816), (5, 4, 1, 27632, 3072), (5, 4, 2, 15344, 4096),
+    (6, 1, 1, 48, 1280), (6, 1, 4, 48, 11008), (6, 2, 1, 9200, 512), (6, 2, 3, 5104, 2048), (6, 3, 1, 20464, 8192),
+    (6, 3, 4, 6128, 2048),
+]
+
+
+@pytest.mark.parametrize("fm,cb,S,N,K", STREAMED)
+def test_bf16_streamed_instances(fm, cb, S, N, K):
+    """Every reachable instance, unsplit and split, at its first and last row count; N ends inside a
+    column block or a tile."""
+    for M in (32 * fm - 31, 32 * fm):
+        assert stream_plan(EPI_STORE, M, N, K) == (fm, cb, S)
+        x = wl.draw(("t_inst_x", M, K), (M, K), device="cuda")
+        w = wl.draw(("t_inst_w", N, K), (N, K), std=0.02, device="cuda")
+        y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        af.op_linear(x, w, y)
+        xd, wd = x.double(), w.double()
+        ref = xd @ wd.t()
+        err = (y.double() - ref).abs()
+        assert bool((err <= _bound(xd, wd, ref, torch.bfloat16)).all()), (M, N, K)
+
+
+# rows, d_model, vocabulary and the streaming instance of an LM head (None: the tiles)
+HEADS = [
+    (1, 3072, 48, (1, 1, 1)), (33, 2048, 48, (2, 1, 1)), (64, 256, 9200, (2, 2, 1)), (50, 5632, 20464, (2, 3, 1)),
+    (64, 3072, 3072, (2, 2, 4)), (96, 1536, 48, (3, 1, 1)), (65, 256, 9200, (3, 2, 1)), (96, 5632, 20464, (3, 3, 1)),
+    (66, 8192, 27632, (3, 4, 1)), (97, 1280, 48, (4, 1, 1)), (128, 256, 9200, (4, 2, 1)), (100, 5632, 20464, (4, 3, 1)),
+    (128, 2816, 6128, (4, 3, 4)), (129, 1280, 48, (5, 1, 1)), (160, 256, 9200, (5, 2, 1)), (140, 5632, 20464, (5, 3, 1)),
+    (161, 1280, 48, (6, 1, 1)), (192, 512, 9200, (6, 2, 1)), (170, 2048, 6128, (6, 3, 4)),
+    (33, 4096, 32000, None), (64, 4096, 32000, None), (96, 4096, 32000, None), (128, 4096, 32000, None),
+    (192, 4096, 32000, None), (288, 4096, 32000, None),
+]
+
+
+@pytest.mark.parametrize("n,D,V,plan", HEADS)
+def test_bf16_head_of_many_rows(n, D, V, plan):
+    """fp32 logits of n emitting rows, streamed and on the tiles, and the greedy token of each."""
+    assert stream_plan(EPI_STORE_F32, n, V, D) == plan
+    shape = wl.ModelShape(n_layers=0, d_model=D, n_heads=D // 64, head_dim=64, d_ff=64, vocab=V)
+    g = {"embed": torch.zeros((V, D), dtype=torch.bfloat16, device="cuda"),
+         "final_norm": wl.draw(("t_head_g", D), (D,), std=0.1, mean=1.0, device="cuda"),
+         "lm_head": wl.draw(("t_head_w", V, D), (V, D), std=0.02, device="cuda")}
+    w = af.Weights(shape, g, [])
+    hidden = wl.draw(("t_head_x", n, D), (n + 3, D), device="cuda")
+    rows = [(i * 7 + 2) % (n + 3) for i in range(n)] if (n + 3) % 7 else list(range(3, n + 3))
+    segs = [af.Segment(r, 1, i, 0, 1000 + i, af.AF_SEG_EMIT, 0) for i, r in enumerate(rows)]
+    z = torch.full((n + 1, V), 7.0, dtype=torch.float32, device="cuda")
+    toks = torch.empty(n, dtype=torch.int32, device="cuda")
+    af.op_lm_head_argmax(w, hidden, segs, z, toks)
+    # the normed rows as the library stores them
+    xn = torch.empty((n, D), dtype=torch.bfloat16, device="cuda")
+    af.op_rmsnorm(hidden[rows].contiguous(), g["final_norm"], xn, shape.rms_eps)
+    torch.cuda.synchronize()
+    xd, wd = xn.double(), g["lm_head"].double()
+    ref = xd @ wd.t()
+    err = (z[:n].double() - ref).abs()
+    assert bool((err <= _bound(xd, wd, ref, torch.float32)).all())
+    assert bool((z[n] == 7.0).all())  # nothing past the last row
+    # ties between fp32 logits: the lowest index
+    assert torch.equal(toks.long(), torch.argmax((z[:n] == z[:n].max(dim=1, keepdim=True).values).float(), dim=1))
+    w.close()
+
+
 @pytest.mark.parametrize("M", [1, 2, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193])
 @pytest.mark.parametrize("N,K", [(48, 256), (608, 4096), (4096, 1024)])
 def test_bf16_row_block_edges(M, N, K):
-    """Every instance's first and last row count; a last column block half past N (48), tiles past
+    """Row counts at the edges of row blocks; a last column block half past N (48), tiles past
     the last column block (608 = 19 blocks), split and unsplit K."""
     _check(M, N, K, torch.bfloat16)
 
@@ -42,8 +123,7 @@ def test_bf16_row_block_edges(M, N, K):
 @pytest.mark.parametrize("M", [7, 135, 192])
 @pytest.mark.parametrize("N,K", [(4096, 11008), (12288, 4096), (22016, 256), (32000, 512)])
 def test_bf16_projection_widths(M, N, K):
-    """The 7B projections' widths with their K splits (11008: shares of 43 k units), and widths
-    that take three and four column blocks per tile."""
+    """The 7B projections' widths with their K splits (11008: shares of 43 k units), and wide ones."""
     _check(M, N, K, torch.bfloat16)
 
 
@@ -60,12 +140,14 @@ def test_bf16_two_k_groups(M, N, K):
 def test_f32_small_tiles(M, N, K):
     """Row and column remainders of the 16 x 32 tile; K below, at and past what a wave requests at
     once (two steps of 32 at K <= 256, six beyond, and more than one such share)."""
+    assert f32_small(M, N, K)
     _check(M, N, K, torch.float32)
 
 
 @pytest.mark.parametrize("M,N,K", [(32, 16384, 512), (24, 6144, 1024), (80, 6144, 2048), (144, 3072, 2048)])
 def test_f32_wide_tiles_of_few_rows(M, N, K):
     """Few rows that the 32- and 96-row fp32 tiles do faster than the 16 x 32 ones, K split and not."""
+    assert not f32_small(M, N, K)
     _check(M, N, K, torch.float32)
 
 

@@ -5,6 +5,7 @@
   ring of 16 slots x 544 positions pre-filled with N(0, 1) keys/values whose slots wrap:
   hidden states against the oracle's packed layer, every written ring cell against the
   oracle's, every other cell bit-for-bit untouched.
+* Few rows: layers of 40 to 172 rows, one for each plan of the streamed projections.
 * Stress step (one 7B-shape layer): 8 pipelines x (276 prefill + 7 decode rows), M = 2264,
   ring 64 x 288, against the oracle.
 * Stress pipeline (32 layers, the full size): the 8 pipelines packed into each forward give
@@ -20,6 +21,7 @@ import oracle
 import workload as wl
 from tests.helpers import (advance_head, allclose_report, bf16_layer_parity, oracle_model, oracle_segments,
                            reserve_step, to_np)
+from tests.plans import EPI_QKV, EPI_SWIGLU, stream_plan
 
 pytestmark = pytest.mark.gpu
 af = pytest.importorskip("paper_2512_20276_amd")
@@ -93,6 +95,24 @@ def test_sweep_point_matches_oracle(layer7b, sweep_history, P, d):
     segs = _run_layer(shape, w, model, sweep_history, n_slots, max_pos, specs, head_shift=(7 * P + d) % n_slots,
                       key=("sweep rows", P, d))
     assert len(segs) == d + (P > 0)
+
+
+@pytest.mark.parametrize("P,ctx,d,qkv,gu", [
+    (0, 0, 40, (2, 2, 1), (2, 3, 1)), (60, 0, 4, (2, 2, 1), (2, 3, 1)), (70, 0, 5, (3, 3, 2), (3, 3, 1)),
+    (87, 0, 3, (3, 2, 1), (3, 3, 1)), (100, 200, 3, (4, 3, 2), (4, 3, 1)), (120, 0, 8, (4, 3, 2), (4, 3, 1)),
+    (150, 0, 10, (5, 3, 2), (5, 3, 1)), (165, 0, 7, None, None)])
+def test_few_row_layers_match_oracle(layer7b, sweep_history, P, ctx, d, qkv, gu):
+    """Layers of 40 to 172 rows: every plan of the streamed QKV and gate/up projections of the 7B
+    shape (row blocks, column blocks, K splits), with their rotary and SwiGLU epilogues; the output
+    and down projections beside them are split four ways.  At 172 rows all run on the tiles."""
+    shape, w, model = layer7b
+    M = P + d
+    assert stream_plan(EPI_QKV, M, 3 * shape.d_model, shape.d_model) == qkv
+    assert stream_plan(EPI_SWIGLU, M, 2 * shape.d_ff, shape.d_model) == gu
+    n_slots, max_pos = (48, 320) if d > 15 else wl.SWEEP_RING
+    hist = _history("few rows history", n_slots, max_pos, shape.n_heads, shape.head_dim) if d > 15 else sweep_history
+    specs = ([(900, ctx, P)] if P else []) + [(901 + i, 20 + 7 * i, 1) for i in range(d)]
+    _run_layer(shape, w, model, hist, n_slots, max_pos, specs, head_shift=3, key=("few rows", P, d))
 
 
 def test_stress_step_layer_matches_oracle(layer7b):
