@@ -70,14 +70,19 @@ def parse():
 
 
 COPY_BYTES = 1 << 30        # calibration copy: 1 GiB read + 1 GiB written, far beyond the 256 MB last-level cache
-KERNELS_SRC = os.path.join(ROOT, "paper_2512_20276_amd", "csrc", "af_gemm.hip")
+# what the gate/up GEMM of the step is compiled from: its source and every header that it takes in
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2512_20276_amd", "csrc", n)
+                  for n in ("af_gemm.hip", "af_epilogue.h", "af_device.h", "af_internal.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_gemm_gateup_7b_m282.md")
 
 
 def kernels_sha256():
     import hashlib
-    with open(KERNELS_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNEL_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic():
@@ -97,7 +102,9 @@ def _kernel_class(name: str) -> str:
     """Maps a kernel name (mangled or demangled) to the label used in the summaries."""
     import re
     if "gemm_stream_kernel" in name:  # its epilogue is an argument
-        return "gemm (up to 192 rows)"
+        fm, cb = (re.search(r"gemm_stream_kernelILi(\d+)ELi(\d+)E", name)
+                  or re.search(r"gemm_stream_kernel<(\d+), (\d+)", name)).groups()
+        return f"gemm (streamed, {fm} row x {cb} column blocks)"
     if "gemm_f32_small_kernel" in name:
         return "gemm (fp32, small model)"
     if any(k in name for k in ("gemm_kernel", "gemm32_kernel", "gemm32x2_kernel", "gemm32c_kernel",
