@@ -80,6 +80,11 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
   return x * q + (x < r ? x : r) + j;
 }
 
+// 16 bytes per lane from p + voff to LDS at dst + 16 * lane; counted by vmcnt.  (m0 is reserved: the
+// compiler keeps nothing in it from one of its own uses to the next.)
+__device__ __forceinline__ void dma16(const void* p, unsigned voff, unsigned dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(p) : "memory");
+}
 
 // 8 consecutive elements with 16-byte (bf16) or 32-byte (fp32) accesses.
 template <typename T>

@@ -4,11 +4,8 @@
 
 namespace af {
 
-// 16 bytes per lane from p + voff, to LDS at dst + 16 * lane or to registers; counted by vmcnt.
-__device__ __forceinline__ void dma16(const void* p, unsigned voff, unsigned dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(p) : "memory");
-}
-// (the register is an in-out operand, so that a refill stays in the registers of its ring slot)
+// 16 bytes per lane from p + voff; counted by vmcnt.  (The register is an in-out operand, so that a
+// refill stays in the registers of its ring slot.)
 __device__ __forceinline__ void load16(bf16x8& v, const void* p, unsigned voff) {
   asm volatile("global_load_dwordx4 %0, %1, %2" : "+v"(v) : "v"(voff), "s"(p) : "memory");
 }

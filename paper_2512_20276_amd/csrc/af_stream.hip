@@ -4,11 +4,6 @@
 
 namespace af {
 
-// 16 bytes per lane from p + voff to LDS at dst + 16 * lane; counted by vmcnt.
-__device__ __forceinline__ void dma16(const char* p, unsigned voff, unsigned dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(p) : "memory");
-}
-
 // acc += w . x over 16 k with the accumulator held in AGPRs (AG) or VGPRs.
 template <bool AG>
 __device__ __forceinline__ void mma(f32x16& acc, bf16x8 w, bf16x8 x) {
