@@ -197,11 +197,15 @@ af_status af_packed_layer_forward_kv(af_weights* w, int32_t layer, void* hidden_
                                      void* hip_stream);
 
 /* Options of the forward (bit flags; default 0):
- *  AF_OPT_NO_SPLIT_K  never split a projection's K range over workgroups.  Every kernel then
- *                     computes a row exactly as it would with no other rows packed beside it
- *                     (bit-identical), at some cost in parallelism for small packed steps.  By
- *                     default, projections with too few output tiles to fill the GPU sum fp32
- *                     partials over K splits (deterministic, but in another order). */
+ *  AF_OPT_NO_SPLIT_K  run projections only on kernels that sum K in the one order they share, and
+ *                     never split K over workgroups.  Every kernel then computes a row exactly
+ *                     as it would with no other rows packed beside it (bit-identical).  By default
+ *                     the order of the sum over K depends on how many rows are packed, at any
+ *                     size: over workgroups where there are few output tiles, and over the waves
+ *                     of one in the kernels for few rows, for small fp32 models and for many rows
+ *                     (deterministic, but in other orders).  The option costs parallelism in small
+ *                     packed steps and those kernels everywhere: bf16 steps of up to 192 rows,
+ *                     small fp32 steps and steps of more than 256 rows are slower with it. */
 #define AF_OPT_NO_SPLIT_K 1u
 af_status af_weights_set_options(af_weights* w, uint32_t flags);
 

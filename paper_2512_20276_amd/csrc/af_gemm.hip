@@ -860,7 +860,8 @@ static int wide_plan(int epi, const GemmArgs& a) {
 }
 
 // 288 x 128 tiles: with two k groups of waves, or in the one order of summation that every other
-// tile shape shares (and for the fp32 store, which no path takes at this many rows).
+// tile shape shares.  The fp32 store (an LM head of more than 256 emitting rows) has no instance
+// with k groups.
 static hipError_t gemm_launch_9(int epi, const GemmArgs& a, hipStream_t s) {
   if (!a.fixed_order && epi != EPI_STORE_F32) return launch_gemm_ksplit(epi, a, s);
   return gemm32_launch<9, true>(epi, a, s);
