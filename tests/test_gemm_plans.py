@@ -44,6 +44,7 @@ def test_tiles_where_streaming_is_slower(epi, M, N, K):
     (EPI_QKV, 192, 24576, 8192, (6, 3, 1)),      # 123.5, 117.4
     (EPI_STORE_F32, 33, 4096, 1024, (2, 1, 1)),  # 11.2, 7.5
     (EPI_STORE_F32, 96, 22016, 5120, (3, 3, 1)),  # 83.2, 80.1
+    (EPI_STORE_F32, 64, 32000, 4096, (2, 4, 1)),  # with norm and argmax 61.7, 60.8
 ])
 def test_streamed_where_it_is_faster(epi, M, N, K, plan):
     assert stream_plan(epi, M, N, K) == plan

@@ -78,7 +78,7 @@ HEADS = [
     (66, 8192, 27632, (3, 4, 1)), (97, 1280, 48, (4, 1, 1)), (128, 256, 9200, (4, 2, 1)), (100, 5632, 20464, (4, 3, 1)),
     (128, 2816, 6128, (4, 3, 4)), (129, 1280, 48, (5, 1, 1)), (160, 256, 9200, (5, 2, 1)), (140, 5632, 20464, (5, 3, 1)),
     (161, 1280, 48, (6, 1, 1)), (192, 512, 9200, (6, 2, 1)), (170, 2048, 6128, (6, 3, 4)),
-    (33, 4096, 32000, None), (64, 4096, 32000, None), (96, 4096, 32000, None), (128, 4096, 32000, None),
+    (33, 4096, 32000, (2, 4, 1)), (64, 4096, 32000, (2, 4, 1)), (96, 4096, 32000, None), (128, 4096, 32000, None),
     (192, 4096, 32000, None), (288, 4096, 32000, None),
 ]
 
