@@ -29,9 +29,11 @@ __device__ __forceinline__ void load16(bf16x8& v, const void* p, unsigned voff) 
 // K = 11008, 12288 columns 227.8 -> 209.5; 527 rows, 4096 columns, K = 11008 in four splits 61.2 ->
 // 57.7.  It sums k in another order than the other tiles, so it is not taken with fixed_order.
 //
-// Measured for KG = 1 at K = 4096, 2264 rows, against waves of one column block: 12288 columns 225.6 -> 215.6 us, 22016 columns
-// 358.8 -> 345.0.  The MFMAs are busy 70 % of a full pass (62 % before), and what that saves in
-// cycles the clock gives back in part (2.01 -> 1.93 GHz): the chip is at its power limit.
+// Measured for KG = 1 at K = 4096, 2264 rows, against waves of one column block: 12288 columns 225.6 ->
+// 215.6 us, 22016 columns 358.8 -> 345.0.  In the packed step of that size the matrix cores are busy 60 %
+// of the gate/up launch's cycles (54 % before), with the last of its three passes 69 % full, and 48 %
+// in the output and down projections on KG = 2 (42 %); the clock gives part of it back (1.96 -> 1.87
+// and 2.17 -> 2.07 GHz): the chip is at its power limit.
 template <int KG, int EPI>
 __global__ __launch_bounds__(512, 1) void gemm32w_kernel(GemmArgs a) {
   constexpr int FM = 9, KS = 4, NBUF = 4, PFB = 4, BLK = 512, TN = 256 / KG, PB = 3;

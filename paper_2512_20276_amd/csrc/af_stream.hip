@@ -24,17 +24,19 @@ __device__ __forceinline__ void pin(f32x16& acc) {
 // x 32 CB columns x one K split, so every weight is loaded by one CU only, and its four waves take
 // the 16-wide k steps in turn: no fragment, of weights or activations, is used by two waves, so
 // each wave streams both through an LDS ring of its own (up to 40 KB, R steps, filled by
-// global_load_lds) without a barrier, and 120 to 160 KB per CU are in flight.  The accumulators of
+// global_load_lds) without a barrier: up to 160 KB per CU are requested ahead.  The accumulators of
 // the whole tile sit in every wave (FM CB x 16 registers, one wave per SIMD) and are summed through
 // LDS at the end, RB row blocks at a time.  The product is taken with the weights as first operand,
 // so that a lane holds four consecutive columns of a row and the sums are parked and read back
 // with 16-byte accesses.
 //
-// Weights and activations of a CU share one in-order path of about 39 KB in flight (a stream of
-// weights alone runs at 72 GB/s per CU, activations from L2 at 164, and a mix of the two near the
-// slower rate for all its bytes), so a tile's cost is (FM + CB) fragments a step: from seven row
-// blocks on, two row tiles that share the weights through L2 (gemm32c_kernel) move fewer bytes
-// per CU and are faster (250 rows, gate/up: 59.9 against 62.6 us here).
+// What bounds it is the reads of 128 bytes that a CU keeps on their way, however many are requested
+// (counters of layers of 1 to 15 and of 129 to 143 rows): with one row block 81 to 99, at 1130 to
+// 1310 cycles each, since nearly all come from HBM; with five 62 to 66, at 550 to 610, as in the
+// tiles that split K over workgroups only; the matrix cores are busy 6 and 16 to 20 % of the time.
+// So a tile's cost is its (FM + CB) fragments a step, and from six row blocks on two row tiles that
+// share the weights through L2 (gemm32c_kernel) move no more bytes per CU and are as fast (192 rows,
+// QKV of the 7B shape: 44.4 against 44.5 us here).
 //
 // FM <= 5: the step's fragments are read, then its ring slot is refilled, then the MFMAs run.
 // FM = 6: there the MFMAs matter (18 per step and wave), so fragment reads run two row blocks
@@ -42,7 +44,8 @@ __device__ __forceinline__ void pin(f32x16& acc) {
 //
 // Measured for one 7B layer against the tiles of 128 columns split over K (gemm32_kernel,
 // gemm32x2_kernel): 1 row 113.9 -> 103.3 us, 15 rows 125.3 -> 114.7, 103 rows 178.7 -> 161.3, 135 rows
-// 183.7 -> 173.9; gate/up at 135 rows 59 -> 56 us, at 15 rows 34.9 -> 32.2 (5.6 TB/s of weights).
+// 183.7 -> 173.9; gate/up at 160 rows 60.7 -> 56.0 us, at 64 rows 48.0 -> 38.1, at 16 rows 36.0 ->
+// 34.0 (5.3 TB/s of weights).
 template <int FM, int CB, int R>
 __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(GemmArgs a, int epi) {
   constexpr int E = FM + CB;          // 1 KB fragments per k step: CB of weights, then FM of activations
