@@ -295,25 +295,28 @@ static hipError_t stream_launch_cb(int cb, int epi, const GemmArgs& a, hipStream
 //    they pay over long K only (96 rows, N 8192: K 28672 97.8 -> 91.7, K 8192 42.0 -> 46.9), and with
 //    fewer workgroups than the tiles not at all (160 rows, N 5120, K 13824 51.0 -> 53.6).
 //  - Six row blocks: a tile of at most 96 columns.  Two passes of it for one of the tiles': N 27648,
-//    K 5120 84.6 -> 103.6, LM head N 32000, K 4096 71.6 -> 89.4.  Wide or split tiles are no faster
-//    than the 160-row tiles (7B shape: QKV 42.2 -> 42.8, O 25.6 -> 25.9, N 3072, K 3072 21.6 -> 23.0);
-//    narrow ones are (N 11008, K 2048 30.4 -> 26.2), wide ones over long K (N 24576, K 8192
-//    123.5 -> 117.4), and split ones against the 224-row tiles over short K (N 6144, K 2048
-//    29.3 -> 26.6; K 8192 56.5 -> 58.9).
+//    K 5120 84.6 -> 103.6, LM head N 32000, K 4096 71.6 -> 89.4.  Split ones are no faster than the
+//    160-row tiles (a layer of d 3072 with O streamed 128.1 -> 129.8); narrow ones are (N 11008, K 2048
+//    30.4 -> 26.2), wide ones over long K (a 7B layer of 192 rows with gate/up streamed 179.5 -> 177.5,
+//    N 24576, K 8192 123.5 -> 117.4), and split ones against the 224-row tiles unless their workgroups
+//    are fewer (N 6144, K 2048 29.3 -> 26.6; d 6144, 192 rows, down 70.1 -> 66.8; d 5120 53.7 -> 56.5)
+//    or two column blocks go over long K (K 8192 56.5 -> 58.9).
 //  - Short K: the waves' sums outweigh it.  Tiles that fill the GPU unsplit: 160 rows, N 27648, K 512
 //    16.6 -> 20.3, K 2048 36.1 -> 37.5; N 22016, K 512 15.4 -> 17.5 (64 rows 12.5 -> 11.6).  One row
-//    block at K 256, where a wave has four steps of a ring of up to twenty: N 768 6.3 -> 6.9.
+//    block at K 256, where a wave has four steps of a ring of up to twenty: N 768 6.3 -> 6.9; before a
+//    residual also at K up to 1536, where the tiles' split sums are added in the norm that follows (a
+//    layer of d 1024, 16 rows, with O streamed 37.9 -> 38.6; of d 512, one row, with down 31.0 -> 32.1).
 static bool stream_pays(const StreamPlan& p, int wg, int Kp, int epi, const TilePlan& tiles) {
   const bool full = tiles.splits == 1 && tiles.wg >= 160;  // the tiles fill the GPU unsplit
-  if (p.fm == 1 && Kp <= 256) return false;
+  if (p.fm == 1 && Kp <= (epi == EPI_RESID ? 1536 : 256)) return false;
   if (epi == EPI_STORE_F32) {
     if (full) return p.fm > 1 && p.fm < 6 && Kp >= (p.cb == 3 || p.fm == 3 ? 5120 : p.fm == 2 ? 4096 : 8192);
     if (p.cb == 4) return false;
   }
   if (p.fm == 6) {
     if (wg > 256) return false;
-    if (p.splits == 1) return p.cb == 1 || (p.cb == 2 ? Kp <= 6144 : Kp >= 8192);
-    return p.cb == 1 || (tiles.fm == 7 && Kp <= 3072);
+    if (p.splits == 1) return p.cb == 1 || (p.cb == 2 ? Kp <= 6144 : Kp >= 4096);
+    return p.cb == 1 || (tiles.fm == 7 && (p.cb == 2 ? Kp <= 3072 : wg >= tiles.wg));
   }
   // one row block, 128 columns, unsplit: the tile's waves share the activations and it is 1 % faster
   // (61.5 against 62.1 us for the LM head of 7 rows with its norm and argmax)

@@ -26,6 +26,8 @@ from tests.plans import (EPI_QKV, EPI_RESID, EPI_STORE_F32, EPI_SWIGLU, f32_smal
     (EPI_SWIGLU, 160, 27648, 512),       # 16.6, 20.3
     (EPI_SWIGLU, 160, 22016, 512),       # 15.4, 17.5
     (EPI_QKV, 1, 768, 256),              # 6.3, 6.9
+    (EPI_RESID, 16, 1024, 1024),         # a layer 37.9, 38.6
+    (EPI_RESID, 192, 5120, 13824),       # 53.7, 56.5
 ])
 def test_tiles_where_streaming_is_slower(epi, M, N, K):
     assert stream_plan(epi, M, N, K) is None
@@ -42,6 +44,8 @@ def test_tiles_where_streaming_is_slower(epi, M, N, K):
     (EPI_SWIGLU, 192, 11008, 2048, (6, 2, 1)),   # 30.4, 26.2
     (EPI_QKV, 192, 6144, 2048, (6, 3, 4)),       # 29.3, 26.6
     (EPI_QKV, 192, 24576, 8192, (6, 3, 1)),      # 123.5, 117.4
+    (EPI_SWIGLU, 192, 22016, 4096, (6, 3, 1)),   # a layer 179.5, 177.5
+    (EPI_RESID, 192, 6144, 16384, (6, 3, 4)),    # 70.1, 66.8
     (EPI_STORE_F32, 33, 4096, 1024, (2, 1, 1)),  # 11.2, 7.5
     (EPI_STORE_F32, 96, 22016, 5120, (3, 3, 1)),  # 83.2, 80.1
     (EPI_STORE_F32, 64, 32000, 4096, (2, 4, 1)),  # with norm and argmax 61.7, 60.8
