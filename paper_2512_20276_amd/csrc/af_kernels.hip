@@ -402,10 +402,12 @@ hipError_t launch_embed(int dtype, const int32_t* ids, const void* table, int vo
 // One workgroup of 1024 threads per row, 16-byte loads; the lowest index among equal maxima wins
 // (each thread scans its indices in increasing order and keeps the first maximum it meets; the
 // reduction prefers the lower index on equal values).  A few rows leave nothing but latency: every
-// thread requests UN chunks (its whole share of a 32000-wide row) before it compares any, one
-// memory latency instead of eight (7 rows of 32000: 6.5 -> 4.9 us).
+// thread requests UN chunks before it compares any, its whole share of a row of up to 32768, one
+// memory latency instead of eight (7 rows of 32000: 6.5 -> 4.9 us).  UN is no more than a thread's
+// share: eight for every width repeated a 4096-wide row's one chunk seven times (2000 rows: 16.1 ->
+// 19.9 us).
+template <int UN>
 __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ logits, int V, int32_t* tokens) {
-  constexpr int UN = 8;
   __shared__ float sv[16];
   __shared__ int si[16];
   const float* z = logits + (size_t)blockIdx.x * V;
@@ -453,7 +455,13 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
 
 hipError_t launch_argmax(const float* logits, int n_rows, int V, int32_t* tokens, hipStream_t s) {
   if (n_rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(argmax_kernel, dim3(n_rows), dim3(1024), 0, s, logits, V, tokens);
+  const dim3 grid(n_rows), block(1024);
+  if (V <= 4096)
+    hipLaunchKernelGGL(argmax_kernel<1>, grid, block, 0, s, logits, V, tokens);
+  else if (V <= 16384)
+    hipLaunchKernelGGL(argmax_kernel<4>, grid, block, 0, s, logits, V, tokens);
+  else
+    hipLaunchKernelGGL(argmax_kernel<8>, grid, block, 0, s, logits, V, tokens);
   return hipGetLastError();
 }
 

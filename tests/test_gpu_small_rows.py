@@ -33,6 +33,32 @@ def _check(M, N, K, dt):
     assert bool((err <= bound).all()), (M, N, K, float((err - bound).max()))
 
 
+@pytest.mark.parametrize("V", [16, 4080, 4096, 4112, 16384, 16400, 32768, 32784, 65552])
+def test_argmax_widths(V):
+    """Tokens at the widths where a thread's share of chunks changes: ties at the first and the last
+    column, rows of equal, of infinite and of NaN logits."""
+    D = 64
+    shape = wl.ModelShape(n_layers=0, d_model=D, n_heads=1, head_dim=64, d_ff=64, vocab=V, dtype="f32")
+    head = wl.draw(("t_argmax_w", V), (V, D), dtype=torch.float32, device="cuda")
+    head[V - 1] = head[0]  # the same logit in the first and the last column
+    g = {"embed": torch.zeros((V, D), device="cuda"), "final_norm": torch.ones(D, device="cuda"), "lm_head": head}
+    w = af.Weights(shape, g, [])
+    n = 70
+    hidden = wl.draw(("t_argmax_x", V), (n, D), dtype=torch.float32, device="cuda")
+    hidden[0] = head[0] * 10    # the tied columns win
+    hidden[1] = 0.0             # every logit equal
+    hidden[2] = float("nan")    # no logit is comparable
+    z = torch.empty((n, V), dtype=torch.float32, device="cuda")
+    toks = torch.empty(n, dtype=torch.int32, device="cuda")
+    af.op_lm_head_argmax(w, hidden, [af.Segment(i, 1, i, 0, 100 + i, af.AF_SEG_EMIT, 0) for i in range(n)], z, toks)
+    torch.cuda.synchronize()
+    best = z.max(dim=1, keepdim=True).values
+    want = torch.argmax((z == best).float(), dim=1)
+    assert want[0] == 0 and want[1] == 0 and want[2] == 0  # the lowest index; 0 where nothing compares
+    assert torch.equal(toks.long(), want)
+    w.close()
+
+
 def _bound(x, w, ref, dt):
     """What the exact value and a result may differ by (float64 on the GPU)."""
     b = (x.shape[1] + 8) * 2.0 ** -24 * (x.abs() @ w.abs().t())
