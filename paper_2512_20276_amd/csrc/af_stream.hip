@@ -289,7 +289,9 @@ static hipError_t stream_launch_cb(int cb, int epi, const GemmArgs& a, hipStream
 //    26.9 -> 29.8 at K 2048 (cached), 90.5 -> 93.4 at K 4096 (displaced).  Storing a tile's fp32
 //    logits and adding the waves' sums cost the same at any K, so only long K pays, the longer the
 //    more row blocks (64 rows, K 4096, with norm and argmax 61.7 -> 60.8; 128 rows, K 8192
-//    149.3 -> 146.2; 96-column tiles, N 22016, K 5120 83.2 -> 80.1), and with one row block none.
+//    149.3 -> 146.2), and with one row block none.  Where the tiles leave a third of the GPU idle, on
+//    96-column tiles, from K 1024 on (N 22016: 64 rows, K 1024, with norm and argmax 28.2 -> 26.2;
+//    96 rows, K 5120 83.2 -> 80.1).
 //    Split heads on 128-column tiles: 128 rows, N 8192, K 4096 35.7 -> 39.5.
 //  - 128-column streamed tiles share less than the tiles of that width do.  Split more than two ways
 //    they pay over long K only (96 rows, N 8192: K 28672 97.8 -> 91.7, K 8192 42.0 -> 46.9), and with
@@ -310,6 +312,7 @@ static bool stream_pays(const StreamPlan& p, int wg, int Kp, int epi, const Tile
   const bool full = tiles.splits == 1 && tiles.wg >= 160;  // the tiles fill the GPU unsplit
   if (p.fm == 1 && Kp <= (epi == EPI_RESID ? 1536 : 256)) return false;
   if (epi == EPI_STORE_F32) {
+    if (full && p.cb == 3 && p.fm < 6 && tiles.wg < 180) return Kp >= (p.fm <= 3 ? 1024 : 2048);
     if (full) return p.fm > 1 && p.fm < 6 && Kp >= (p.cb == 3 || p.fm == 3 ? 5120 : p.fm == 2 ? 4096 : 8192);
     if (p.cb == 4) return false;
   }

@@ -48,6 +48,7 @@ def test_tiles_where_streaming_is_slower(epi, M, N, K):
     (EPI_RESID, 192, 6144, 16384, (6, 3, 4)),    # 70.1, 66.8
     (EPI_STORE_F32, 33, 4096, 1024, (2, 1, 1)),  # 11.2, 7.5
     (EPI_STORE_F32, 96, 22016, 5120, (3, 3, 1)),  # 83.2, 80.1
+    (EPI_STORE_F32, 64, 22016, 1024, (2, 3, 1)),  # with norm and argmax 28.2, 26.2
     (EPI_STORE_F32, 64, 32000, 4096, (2, 4, 1)),  # with norm and argmax 61.7, 60.8
 ])
 def test_streamed_where_it_is_faster(epi, M, N, K, plan):
