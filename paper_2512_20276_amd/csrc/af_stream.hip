@@ -34,9 +34,9 @@ __device__ __forceinline__ void pin(f32x16& acc) {
 // (counters of layers of 1 to 15 and of 129 to 143 rows): with one row block 81 to 99, at 1130 to
 // 1310 cycles each, since nearly all come from HBM; with five 62 to 66, at 550 to 610, as in the
 // tiles that split K over workgroups only; the matrix cores are busy 6 and 16 to 20 % of the time.
-// So a tile's cost is its (FM + CB) fragments a step, and from six row blocks on two row tiles that
-// share the weights through L2 (gemm32c_kernel) move no more bytes per CU and are as fast (192 rows,
-// QKV of the 7B shape: 44.4 against 44.5 us here).
+// So a tile's cost is its (FM + CB) fragments a step, and with six row blocks two row tiles that
+// share the weights through L2 (gemm32c_kernel) move no more bytes per CU and are as fast where K is
+// split (192 rows, QKV of the 7B shape: 44.4 against 44.5 us here).
 //
 // FM <= 5: the step's fragments are read, then its ring slot is refilled, then the MFMAs run.
 // FM = 6: there the MFMAs matter (18 per step and wave), so fragment reads run two row blocks
